@@ -64,7 +64,9 @@ typedef enum {
   ALS_MODE_TIME = 2   /* solve T (one row per time bin) with U and V fixed */
 } als_mode;
 
-/* Tunables of the degree-bucketed schedule. Zero fields select defaults. */
+/* Tunables of the degree-bucketed schedule. Zero fields select defaults; with threshold and
+ * chunk both zero, a matrix too small to keep the GPU busy with rows of 8192 ratings gets a
+ * finer split (down to 512 and 256). */
 typedef struct {
   int32_t hub_threshold;   /* rows with more ratings are split into chunks (default 8192) */
   int32_t chunk;           /* ratings per chunk of a split row (default 4096) */
@@ -159,9 +161,9 @@ als_status als_plan_stats(als_ctx *ctx, als_side side, int64_t *out, int32_t n);
  * Optional per-phase timing with HIP events recorded on the context's stream
  * around each kernel launch (no synchronisation while enabled). Phases:
  * 0 = staging of the fixed side; 1 = gather kernels (D <= 20: the normal
- * equations of every row and chunk; D > 20: those of split-row chunks);
+ * equations of every row and chunk; D > 20: the sums of split rows' chunks);
  * 2 = solve kernels (D <= 20: one row per lane; D > 20: the fused row kernel,
- * which also builds the normal equations of unsplit rows); 3 = new-state
+ * which also builds the normal equations of rows and chunks); 3 = new-state
  * residual pass; 4 = reductions. enable: 0 = off; 1 = every phase; 2 = only the
  * launches that build the normal equations (phase 1, and phase 2 above D = 20), so
  * that no event record sits between the other launches. Other values:

@@ -5,8 +5,8 @@
 // ratings are ordered by descending degree (largest work first); rows above
 // the hub threshold are cut into fixed-size chunks whose partial normal
 // equations go to workspace slots. A half-sweep stages the fixed side into a
-// padded copy, then runs per batch the chunk kernel and the fused row kernel
-// (rowsolve.hip), and reduces the entering-state squared residuals; the
+// padded copy, then runs per batch the Gram kernel and the one-lane solve (lanesolve.hip) or
+// the fused row kernel (rowsolve.hip), and reduces the entering-state squared residuals; the
 // new-state RMSE is an extra residual pass (residual.hip), run on request.
 #include <hip/hip_runtime.h>
 
@@ -27,8 +27,11 @@ using als::WorkItem;
 
 namespace {
 
-constexpr int32_t kDefaultHubThreshold = 8192;
-constexpr int32_t kDefaultChunk = 4096;
+// Ratings per chunk of a split row; rows of more than two chunks' ratings are split.
+// kMaxChunk where the matrix fills the chip many times over, down to kMinChunk for smaller
+// ones (auto_split).
+constexpr int32_t kMaxChunk = 4096;
+constexpr int32_t kMinChunk = 256;
 constexpr int64_t kDefaultWorkspace = 48LL << 30;
 // cap on the block-by-column count table of the device transpose
 constexpr int64_t kCscTableEntries = 1LL << 29;
@@ -39,6 +42,7 @@ struct Batch {
   int64_t n_gitems;   // chunks + unsplit rows
   int64_t row_off, n_rows;
   int64_t n_split;    // the batch's first n_split rows are split rows
+  int64_t split_off;  // split rows of the earlier batches
   int64_t n_slots;    // workspace slots used by the batch's chunks
 };
 
@@ -58,7 +62,7 @@ struct SidePlan {
   int32_t *d_zero_rows = nullptr;
 };
 
-constexpr int kPhases = 5;  // stage, chunks, rows, residual, reduce
+constexpr int kPhases = 5;  // stage, gather, solve, residual, reduce
 
 struct ProfEvent {
   int phase;
@@ -72,7 +76,8 @@ struct als_ctx {
   int32_t D = 0, DP = 0;
   hipStream_t stream = nullptr;
   int device = 0;
-  als_tuning tune{};
+  int n_cu = 256;
+  als_tuning tune{};  // threshold and chunk both zero: chosen per plan (auto_split)
   std::vector<int64_t> h_row_ptr, h_col_ptr;
   int64_t *d_row_ptr = nullptr;
   int32_t *d_col = nullptr;
@@ -110,8 +115,8 @@ struct als_ctx {
   double prof_ms[kPhases] = {0, 0, 0, 0, 0};
   int64_t prof_n[kPhases] = {0, 0, 0, 0, 0};
   bool phase_timing = false;
-  int64_t cyc_cap = 0;            // rows per array of d_cyc
-  double *d_cyc = nullptr;        // [2 x cyc_cap]: per-row Gram and solve cycles
+  int64_t cyc_cap = 0;            // tasks per array of d_cyc
+  double *d_cyc = nullptr;        // [2 x cyc_cap]: per-task Gram and solve cycles
   double *d_cyc_sum = nullptr;    // [2]
   double *h_cyc_sum = nullptr;    // pinned [2]
   double cyc[2][2] = {{0, 0}, {0, 0}};  // per side: Gram, solve
@@ -214,6 +219,34 @@ void csc_blocking(int64_t n_users, int64_t n_items, int64_t &rows_per_blk, int64
   nblk = (n_users + rows_per_blk - 1) / rows_per_blk;
 }
 
+// Wavefronts that the Gram kernel of a width keeps on a SIMD.
+int gram_waves(const als_ctx *ctx) {
+  if (ctx->lane_solve) return 6;
+  return ctx->DP <= 32 ? 4 : ctx->DP <= 48 ? 3 : 2;
+}
+
+// Split of the long rows where the caller leaves it open. The longest item must be short
+// against the ratings that one wavefront slot of the chip gets in all (its share), or the
+// half-sweep waits for a few waves; a chunk costs its slot's write and read. The share is
+// 43 000 ratings at 263M ratings and D = 20, where chunks stay at kMaxChunk (4096: 7.78 ms a
+// sweep, 512: 8.05); 1600 at 10M, where chunks of 4096 took 534 us a sweep, 1024 351 and 256
+// 362; 160 at 1M (tensor ALS, D = 10): 270, 190 and 144 us. Above D = 20 chunks run beside
+// the whole rows' factorisations and their slots are larger: at 1M and D = 33 (share 325)
+// 4096 took 306 us, 512 229 and 256 240; at 5M and D = 50 (share 2441) 942, 878 and 898.
+void auto_split(const als_ctx *ctx, int64_t ratings, int64_t &hub, int64_t &chunk) {
+  const int64_t share = ratings / ((int64_t)ctx->n_cu * 4 * gram_waves(ctx));
+  int64_t c = (ctx->lane_solve ? share * 2 / 3 : share) / 64 * 64;
+  c = std::min<int64_t>(std::max<int64_t>(c, ctx->lane_solve ? kMinChunk : 2 * kMinChunk),
+                        kMaxChunk);
+  // a small workspace coarsens the split again rather than refuse or multiply the batches
+  // (at most ratings / c full chunks and one partial chunk per split row of over 2 c)
+  const int64_t cap = ctx->tune.workspace_bytes / (int64_t)slot_bytes_of(ctx);
+  while (c < kMaxChunk && ratings / c + ratings / (2 * c) + 1 > cap)
+    c = std::min<int64_t>(2 * c, kMaxChunk);
+  chunk = c;
+  hub = 2 * c;
+}
+
 // parity >= 0: only the rows s with s % 2 == parity, and those without ratings are
 // scheduled like the others (the time chain's bins, whose prior depends on the row).
 als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr,
@@ -223,6 +256,7 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
   P.n_rows = n_rows;
   std::vector<int32_t> order;
   order.reserve(n_rows);
+  int64_t ratings = 0;
   for (int64_t s = 0; s < n_rows; ++s) {
     const int64_t d = ptr[s + 1] - ptr[s];
     if (parity >= 0) {
@@ -234,12 +268,16 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
       P.zero_rows.push_back((int32_t)s);
     }
     P.max_deg = std::max(P.max_deg, d);
+    ratings += d;
   }
   std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
     return ptr[a + 1] - ptr[a] > ptr[b + 1] - ptr[b];
   });
   P.rows_with = (int64_t)order.size();
-  const int64_t hub = ctx->tune.hub_threshold, chunk = ctx->tune.chunk;
+  int64_t hub = ctx->tune.hub_threshold, chunk = ctx->tune.chunk;
+  if (!hub && !chunk) auto_split(ctx, ratings, hub, chunk);
+  if (!hub) hub = 2 * kMaxChunk;
+  if (!chunk) chunk = kMaxChunk;
   const int64_t cap = std::max<int64_t>(1, ctx->tune.workspace_bytes / (int64_t)slot_bytes_of(ctx));
   const int64_t max_chunks = P.max_deg > hub ? (P.max_deg + chunk - 1) / chunk : 0;
   if (max_chunks > cap)
@@ -263,7 +301,7 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
     if (first < (int64_t)order.size()) spans.push_back({first, (int64_t)order.size()});
   }
   for (const auto &sp : spans) {
-    Batch b{(int64_t)P.gitems.size(), 0, 0, (int64_t)P.rows.size(), 0, 0, 0};
+    Batch b{(int64_t)P.gitems.size(), 0, 0, (int64_t)P.rows.size(), 0, 0, P.split_rows, 0};
     // chunks of the batch's split rows
     for (int64_t k = sp.first; k < sp.second; ++k) {
       const int32_t s = order[k];
@@ -272,12 +310,10 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
       const int64_t nch = (d + chunk - 1) / chunk;
       ++P.split_rows;
       RowTask rt;
-      rt.start = ptr[s];
       rt.slot0 = b.n_slots;
       rt.row = s;
       rt.deg = (int32_t)d;
       rt.nslots = (int32_t)nch;
-      rt.sse_idx = -1;
       P.rows.push_back(rt);
       for (int64_t q = 0; q < nch; ++q) {
         WorkItem it;
@@ -297,12 +333,10 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
       const int64_t d = ptr[s + 1] - ptr[s];
       if (d > hub) continue;
       RowTask rt;
-      rt.start = ptr[s];
       rt.slot0 = (int64_t)P.rows.size();  // record of the row's packed normal equations
       rt.row = s;
       rt.deg = (int32_t)d;
       rt.nslots = 0;
-      rt.sse_idx = (int32_t)P.gitems.size();
       P.rows.push_back(rt);
       WorkItem it;
       it.start = ptr[s];
@@ -331,6 +365,9 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
                                hipMemcpyHostToDevice));
   return ALS_OK;
 }
+
+// Tasks of the fused row kernel in one half-sweep: the gather items, then the split rows.
+int64_t cycle_tasks(const SidePlan &P) { return (int64_t)P.gitems.size() + P.split_rows; }
 
 // pairs of one predict call: the launch has pair_blocks(n, D) < 2^31 blocks (with up to 8
 // lanes per pair)
@@ -582,8 +619,6 @@ als_status als_create(als_ctx **out, int64_t n_users, int64_t n_items, int64_t n
   c->DP = als::padded_width(D);
   c->lane_solve = als::lane_width(D) > 0;
   c->stream = (hipStream_t)hip_stream;
-  c->tune.hub_threshold = kDefaultHubThreshold;
-  c->tune.chunk = kDefaultChunk;
   c->tune.workspace_bytes = kDefaultWorkspace;
   if (tuning) {
     if (tuning->hub_threshold < 0 || tuning->chunk < 0 || tuning->workspace_bytes < 0) {
@@ -598,6 +633,8 @@ als_status als_create(als_ctx **out, int64_t n_users, int64_t n_items, int64_t n
     delete c;
     return fail(nullptr, ALS_ERR_HIP, "no HIP device");
   }
+  (void)hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->device);
+  c->n_cu = std::max(c->n_cu, 1);
   {
     const hipError_t e = scratch_address(c->device, &c->d_scratch);
     if (e != hipSuccess) {
@@ -665,8 +702,9 @@ als_status als_create(als_ctx **out, int64_t n_users, int64_t n_items, int64_t n
   if (st != ALS_OK) return bail(st);
   st = build_plan(c, c->plan[ALS_ROWS_ITEMS], c->h_col_ptr);
   if (st != ALS_OK) return bail(st);
-  int64_t max_slots = 0, max_sse = 0, max_rows = 0;
+  int64_t max_slots = 0, max_sse = 0, max_rows = 0, max_tasks = 0;
   for (auto &P : c->plan) {
+    max_tasks = std::max(max_tasks, cycle_tasks(P));
     max_slots = std::max(max_slots, P.max_slots);
     max_sse = std::max(max_sse, (int64_t)P.gitems.size());
     max_rows = std::max(max_rows, (int64_t)P.rows.size());
@@ -677,7 +715,7 @@ als_status als_create(als_ctx **out, int64_t n_users, int64_t n_items, int64_t n
     CK(dalloc(&c->d_ne, max_rows * (int64_t)als::ne_floats(als::lane_width(D))));
   CK(dalloc(&c->d_fpad, (std::max(n_users, n_items) + 1) * (int64_t)c->DP));
   CK(dalloc(&c->d_sse_items, max_sse));
-  CK(dalloc(&c->d_partials, als::reduce_partials(max_sse)));
+  CK(dalloc(&c->d_partials, als::reduce_partials(max_tasks)));
   CK(dalloc(&c->d_sse_in, 1));
   CK(dalloc(&c->d_sse_total, 1));
   CK(dalloc(&c->d_flag, 1));
@@ -782,21 +820,29 @@ als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out
                                                 out_factors, ctx->d_flag, pr, ctx->stream));
       }
     } else {
-      if (b.n_gchunks > 0) {
-        PhaseTimer t(ctx, 1);
-        HIP_OR_FAIL(ctx, als::launch_gram_chunks(ctx->DP, P.d_gitems + b.gitem_off, b.n_gchunks,
-                                                 idx, val, wts, ctx->d_fpad, n_fixed, out_factors,
-                                                 ctx->D, ctx->d_ws, sse, hd, ctx->stream));
-      }
+      const bool clocks = ctx->phase_timing && side < 2;  // the clocks cover users and items
+      double *cg = clocks ? ctx->d_cyc + b.gitem_off : nullptr;
+      double *cs = clocks ? cg + ctx->cyc_cap : nullptr;
       {
         PhaseTimer t(ctx, 2);
-        const bool clocks = ctx->phase_timing && side < 2;  // the clocks cover users and items
-        double *cg = clocks ? ctx->d_cyc + b.row_off : nullptr;
-        double *cs = clocks ? ctx->d_cyc + ctx->cyc_cap + b.row_off : nullptr;
-        HIP_OR_FAIL(ctx, als::launch_rows(ctx->DP, P.d_rows + b.row_off, b.n_rows, idx, val, wts,
-                                          ctx->d_fpad, n_fixed, ctx->d_ws, ctx->D, lambda,
-                                          out_factors, ctx->d_sse_items, ctx->d_flag, cg, cs,
-                                          pr, hd, ctx->stream));
+        HIP_OR_FAIL(ctx, als::launch_rows(ctx->DP, P.d_gitems + b.gitem_off, b.n_gchunks, nullptr,
+                                          b.n_gitems, idx, val, wts, ctx->d_fpad, n_fixed,
+                                          ctx->d_ws, ctx->D, lambda, out_factors, sse,
+                                          ctx->d_flag, cg, cs, pr, hd, ctx->stream));
+      }
+      if (b.n_split > 0) {
+        {
+          PhaseTimer t(ctx, 1);
+          HIP_OR_FAIL(ctx, als::launch_sum_slots(ctx->DP, ctx->D, P.d_rows + b.row_off, b.n_split,
+                                                 lambda, ctx->d_ws, pr, ctx->stream));
+        }
+        PhaseTimer t(ctx, 2);
+        cg = clocks ? ctx->d_cyc + (int64_t)P.gitems.size() + b.split_off : nullptr;
+        cs = clocks ? cg + ctx->cyc_cap : nullptr;
+        HIP_OR_FAIL(ctx, als::launch_rows(ctx->DP, nullptr, 0, P.d_rows + b.row_off, b.n_split,
+                                          idx, val, wts, ctx->d_fpad, n_fixed, ctx->d_ws, ctx->D,
+                                          lambda, out_factors, sse, ctx->d_flag, cg, cs, pr, hd,
+                                          ctx->stream));
       }
     }
   }
@@ -816,7 +862,7 @@ als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out
   ctx->last_side = side;
   ctx->sse_in_parts = sp.sse_in_part + 1;
   if (ctx->phase_timing && !ctx->lane_solve && !P.rows.empty() && side < 2) {
-    const int64_t nr = (int64_t)P.rows.size();
+    const int64_t nr = cycle_tasks(P);
     HIP_OR_FAIL(ctx, als::launch_reduce(ctx->d_cyc, nr, ctx->d_partials, ctx->d_cyc_sum,
                                         ctx->stream));
     HIP_OR_FAIL(ctx, als::launch_reduce(ctx->d_cyc + ctx->cyc_cap, nr, ctx->d_partials,
@@ -1118,7 +1164,7 @@ als_status als_set_phase_timing(als_ctx *ctx, int32_t enable) {
   DeviceGuard g(ctx->device);
   if (enable && !ctx->d_cyc) {
     const int64_t cap = std::max<int64_t>(
-        1, std::max((int64_t)ctx->plan[0].rows.size(), (int64_t)ctx->plan[1].rows.size()));
+        1, std::max(cycle_tasks(ctx->plan[0]), cycle_tasks(ctx->plan[1])));
     double *cyc = nullptr, *sum = nullptr, *host = nullptr;
     hipError_t e = dalloc(&cyc, 2 * cap);
     if (e == hipSuccess) e = dalloc(&sum, 2);
@@ -1255,8 +1301,9 @@ als_status als_set_time_bins(als_ctx *ctx, int32_t n_bins, const int32_t *bins) 
   if (st == ALS_OK) st = build_plan(ctx, ctx->plan[4], ptr, 1);
   if (st != ALS_OK) return st;
   // shared buffers sized for the time-bin plans too
-  int64_t max_slots = 0, max_sse = 0, max_rows = 0;
+  int64_t max_slots = 0, max_sse = 0, max_rows = 0, max_tasks = 0;
   for (auto &P : ctx->plan) {
+    max_tasks = std::max(max_tasks, cycle_tasks(P));
     max_slots = std::max(max_slots, P.max_slots);
     max_sse = std::max(max_sse, (int64_t)P.gitems.size());
     max_rows = std::max(max_rows, (int64_t)P.rows.size());
@@ -1281,7 +1328,7 @@ als_status als_set_time_bins(als_ctx *ctx, int32_t n_bins, const int32_t *bins) 
     dfree(ctx->d_sse_items);
     dfree(ctx->d_partials);
     HIP_OR_FAIL(ctx, dalloc(&ctx->d_sse_items, max_sse));
-    HIP_OR_FAIL(ctx, dalloc(&ctx->d_partials, als::reduce_partials(max_sse)));
+    HIP_OR_FAIL(ctx, dalloc(&ctx->d_partials, als::reduce_partials(max_tasks)));
   }
   ctx->n_bins = n_bins;
   return ALS_OK;

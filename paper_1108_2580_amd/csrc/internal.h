@@ -17,17 +17,14 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 24, "WorkItem layout");
 
-// One row to solve. A row with nslots == 0 builds its normal equations from its
-// ratings [start, start + deg); a split row sums nslots workspace slots.
+// One row to solve, from its record (narrow widths) or its workspace slots (split rows).
 struct RowTask {
-  int64_t start;    // first rating of the row
   int64_t slot0;    // batch-local slot of the row's first chunk (split rows)
   int32_t row;
   int32_t deg;      // n_s, number of ratings of the row
-  int32_t nslots;
-  int32_t sse_idx;  // where the row's entering-state squared residuals go (-1: split row)
+  int32_t nslots;   // 0: unsplit
 };
-static_assert(sizeof(RowTask) == 32, "RowTask layout");
+static_assert(sizeof(RowTask) == 24, "RowTask layout");
 
 // The staged fixed side is addressed with 32-bit byte offsets:
 // (rows + 1) * DP * 4 must stay below 2^32.
@@ -94,27 +91,29 @@ hipError_t launch_csc_permute_f32(const int64_t *row_ptr, const int32_t *col, co
 // row n is all zero (rowsolve.hip).
 hipError_t launch_stage_fixed(const float *F, int64_t n, int D, int DP, float *Fp, hipStream_t s);
 
-// Partial normal equations of the chunks of split rows, into their workspace
-// slots, with the chunks' entering-state squared residuals (rowsolve.hip).
+// Fused per-row normal equations, regularisation, Cholesky and solves; X is read
+// (entering state) and overwritten in place (rowsolve.hip). Exactly one of items and rows:
+//  - items: n_tasks gather items. The first n_chunks are chunks of split rows, whose partial
+//    normal equations go to their workspace slots; the others are whole rows, solved at
+//    once. Item i writes its entering-state squared residuals to sse[i].
+//  - rows: n_tasks split rows, whose first slots launch_sum_slots has filled.
 // wts (here and below): per-rating weights aligned with idx / val for weighted ALS,
 // or null for plain ALS.
-hipError_t launch_gram_chunks(int dp, const WorkItem *items, int64_t n, const int32_t *idx,
-                              const uint8_t *val, const float *wts, const float *Fp,
-                              int64_t n_fixed, const float *Xold, int D, float *ws, double *sse,
-                              const Hadamard &hd, hipStream_t s);
-
-// Fused per-row normal equations, regularisation, Cholesky and solves; X is read
-// (entering state) and overwritten in place (rowsolve.hip).
-// cyc_gram / cyc_solve: both null, or arrays of n_rows doubles that receive each
-// row's wavefront clock cycles spent before the factorisation (gather, Gram and
-// residuals, or the sum of chunk partials) and from there on (factorisation, solves,
+// cyc_gram / cyc_solve: both null, or arrays of n_tasks doubles that receive each
+// task's wavefront clock cycles spent before the factorisation (gather, Gram and
+// residuals, or the read of the summed chunks) and from there on (factorisation, solves,
 // write); a measurement aid that leaves the results unchanged.
 // pr: the Bayesian prior (Gibbs half-sweep) or a default RowPrior (ALS; lam is used).
-hipError_t launch_rows(int dp, const RowTask *rows, int64_t n_rows, const int32_t *idx,
-                       const uint8_t *val, const float *wts, const float *Fp, int64_t n_fixed,
-                       const float *ws, int D, float lam, float *X, double *sse, int32_t *flag,
-                       double *cyc_gram, double *cyc_solve, const RowPrior &pr,
-                       const Hadamard &hd, hipStream_t s);
+hipError_t launch_rows(int dp, const WorkItem *items, int64_t n_chunks, const RowTask *rows,
+                       int64_t n_tasks, const int32_t *idx, const uint8_t *val, const float *wts,
+                       const float *Fp, int64_t n_fixed, float *ws, int D, float lam, float *X,
+                       double *sse, int32_t *flag, double *cyc_gram, double *cyc_solve,
+                       const RowPrior &pr, const Hadamard &hd, hipStream_t s);
+
+// The workspace slots of each split row summed into its first slot, with lambda n_s I (or the
+// prior image of pr, without h0 and the right-hand side) added to the tiles (rowsolve.hip).
+hipError_t launch_sum_slots(int dp, int D, const RowTask *rows, int64_t n_split, float lam,
+                            float *ws, const RowPrior &pr, hipStream_t s);
 
 // Per-item sums of squared residuals with the rows of X against the staged
 // fixed side Fp (row stride DP, n_fixed rows and the zero row) (residual.hip).

@@ -204,21 +204,28 @@ void k_gram_ne(const WorkItem *__restrict__ items, int64_t n_chunk_items,
   if (lane == 0) sse_out[blockIdx.x] = sse;
 }
 
-// Sum the chunk records of each split row, in slot order, into the row's record.
+// Sum the chunk records of each split row into the row's record: one block per row, one
+// float4 of the record per lane; the four waves take the slots s = w mod 4 in order, with
+// several slots' loads in flight, and their sums are added in a fixed order.
 template <int LD>
 __global__ __launch_bounds__(256) void k_sum_records(const RowTask *__restrict__ rows, int64_t base,
                                                      const float *__restrict__ ws,
                                                      float *__restrict__ ne) {
-  constexpr int NES = ne_floats(LD);
+  constexpr int NQ = ne_floats(LD) / 4;
+  static_assert(NQ <= 64, "one lane per float4 of a record");
+  __shared__ floatx4 s_part[3][64];
   const RowTask rt = rows[blockIdx.x];
-  for (int e = threadIdx.x; e < NES; e += 256) {
-    // unrolled so that several slots' loads are in flight before their additions, which
-    // stay in slot order
-    float v = 0.f;
+  const int q = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const floatx4 *__restrict__ p =
+      reinterpret_cast<const floatx4 *>(ws) + rt.slot0 * NQ + min(q, NQ - 1);
+  floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 8
-    for (int s = 0; s < rt.nslots; ++s) v += ws[(rt.slot0 + s) * (int64_t)NES + e];
-    ne[(base + blockIdx.x) * (int64_t)NES + e] = v;
-  }
+  for (int s = w; s < rt.nslots; s += 4) v += p[s * (int64_t)NQ];
+  if (w > 0) s_part[w - 1][q] = v;
+  __syncthreads();
+  if (w == 0 && q < NQ)
+    reinterpret_cast<floatx4 *>(ne)[(base + blockIdx.x) * (int64_t)NQ + q] =
+        (v + s_part[0][q]) + (s_part[1][q] + s_part[2][q]);
 }
 
 template <int LD, bool BAYES>

@@ -15,9 +15,9 @@
 //      matrix when a padding feature can carry it); back substitution follows,
 //      from the untouched panel rows A_p and the stored M blocks; x_s is written
 //      unless a pivot was not positive and finite.
-// Rows with more ratings than the hub threshold have their normal equations
-// built by several wavefronts (k_gram_chunks, partials in a workspace) and are
-// only summed and solved here.
+// Rows with more ratings than the hub threshold are cut into chunks: one wavefront per chunk
+// stops after step 1 and stores its partial normal equations in a workspace slot,
+// k_sum_slots adds a row's slots up, and a second launch factors and solves the split rows.
 // STRIP (the last tile holds four used features, D = 16 (T - 1) + 1 .. + 4): the
 // Gram's last tile column is accumulated as 4x4 strips (v_mfma_f32_4x4x1f32) and the
 // right-hand side on VALU, and both are moved into the augmented tile layout before
@@ -68,65 +68,46 @@ __host__ __device__ constexpr int aug_column(int D) {
   return ((D + 3) & ~3) - 16 * (DP / 16 - 1);
 }
 
-// Partial normal equations of the chunks of split rows, with the chunks'
-// entering-state squared residuals.
-template <int DP, bool AUG, bool WT, bool TS, bool STRIP = false>
-__global__ __launch_bounds__(64) void k_gram_chunks(const WorkItem *__restrict__ items,
-                                                    const int32_t *__restrict__ idx,
-                                                    const uint8_t *__restrict__ val,
-                                                    const float *__restrict__ wts,
-                                                    const float *__restrict__ Fp, int zrow,
-                                                    const float *__restrict__ Xold, int D,
-                                                    float *__restrict__ ws,
-                                                    double *__restrict__ sse_out, Hadamard hd) {
-  using C = RowCfg<DP>;
-  constexpr int T = C::T, NT = C::NT;
-  __shared__ GroupStage s_stage;
-  const WorkItem it = items[blockIdx.x];
-  const int lane = threadIdx.x, kq = lane >> 4, c = lane & 15;
-  floatx4 acc[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-  float rhs[T], xo[T];
-#pragma unroll
-  for (int X = 0; X < T; ++X) {
-    rhs[X] = 0.f;
-    {
-      const float v = Xold[(int64_t)it.row * D + min(16 * X + c, D - 1)];
-      xo[X] = 16 * X + c < D ? v : 0.f;
+// The chunks of each split row summed into the row's first slot, with the regulariser (or the
+// prior image) added to the tiles. A block takes one tile (64 float4) of one row's slots; its
+// four waves take the slots s = w mod 4, in order, with several slots' loads in flight, and
+// the four sums are added in a fixed order. Bound by the read of the slots; one wave walking
+// them one by one (28 KB each at D = 100) paid a memory round trip per slot, which only the
+// few slots per row of the coarsest split could afford.
+__global__ __launch_bounds__(256) void k_sum_slots(const RowTask *__restrict__ rows, int T, int D,
+                                                   int nq, int parts, float lam,
+                                                   float *__restrict__ ws, RowPrior pr) {
+  __shared__ floatx4 s_part[3][64];
+  const int task = blockIdx.x / parts, t = blockIdx.x - task * parts;
+  const RowTask rt = rows[task];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int NT = T * (T + 1) / 2, q = t * 64 + lane;
+  const int64_t stride = NT * 64 + T * 4;
+  floatx4 *__restrict__ p =
+      reinterpret_cast<floatx4 *>(ws) + rt.slot0 * stride + (q < nq ? q : nq - 1);
+  floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int s = w; s < rt.nslots; s += 4) v += p[s * stride];
+  if (w > 0) s_part[w - 1][lane] = v;
+  __syncthreads();
+  if (w > 0 || q >= nq) return;
+  v = (v + s_part[0][lane]) + (s_part[1][lane] + s_part[2][lane]);
+  if (t < NT) {
+    if (pr.init != nullptr) {
+      v += pr.scale_of(rt.row) * *reinterpret_cast<const floatx4 *>(pr.init + 4 * q);
+    } else {
+      int I = 0, first = 0;  // tile row I starts with its diagonal tile
+      while (first + T - I <= t) {
+        first += T - I;
+        ++I;
+      }
+      const int c = lane & 15, r = c - 4 * (lane >> 4);
+      if (t == first && r >= 0 && r < 4)
+        v[r] += 16 * I + c < D ? (float)((double)lam * (double)rt.deg) : 1.f;
     }
   }
-  double sse = 0.0;
-  const float *__restrict__ wp = WT ? wts + it.start : nullptr;
-  const int32_t *__restrict__ tp = TS ? hd.idx2 + it.start : nullptr;
-  const GroupLanes g0 =
-      first_group<WT, TS>(idx + it.start, val + it.start, wp, tp, it.len, zrow);
-  float no_corner = 0.f;
-  const int aug_c = AUG ? aug_column<DP>(D) : -1;
-  gram_accumulate<DP, AUG && !STRIP, WT, TS, false, STRIP>(
-      acc, rhs, xo, sse, idx + it.start, val + it.start, wp, tp, it.len, Fp, hd.Tp, zrow,
-      STRIP ? -1 : aug_c, s_stage, g0, no_corner, 0, 0);
-  if constexpr (STRIP) strip_finish<DP>(acc, rhs, aug_c);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sse += __shfl_xor(sse, o);
-  float *__restrict__ out = ws + it.slot * (int64_t)slot_floats(DP);
-#pragma unroll
-  for (int t = 0; t < NT; ++t) *reinterpret_cast<floatx4 *>(out + t * 256 + lane * 4) = acc[t];
-  if constexpr (!AUG) {
-#pragma unroll
-    for (int X = 0; X < T; ++X) {
-      rhs[X] += __shfl_xor(rhs[X], 16);
-      rhs[X] += __shfl_xor(rhs[X], 32);
-    }
-    if (kq == 0) {
-#pragma unroll
-      for (int X = 0; X < T; ++X) out[NT * 256 + 16 * X + c] = rhs[X];
-    }
-  }
-  if (lane == 0) sse_out[blockIdx.x] = sse;
+  *p = v;
 }
-
-constexpr int kRowWaves = 1;  // rows per workgroup (one per wavefront)
 
 // Two wavefronts per SIMD (the second launch bound) outweigh the few registers the
 // wide widths then spill: the accumulator tiles move to arch VGPRs and the gather
@@ -145,12 +126,20 @@ constexpr int kRowWaves = 1;  // rows per workgroup (one per wavefront)
 // forward-substitution result y gets z / sqrt(alpha) before the back substitution, so
 // that the row receives the conditional draw mu* + L*^{-T} z. For the time chain of BPTF
 // the image is scaled per row and a per-row right-hand side h0 is added (RowPrior).
+//
+// The wave's task is one of three. With items (the first launch of a batch): a chunk of a
+// split row, whose normal equations go to its workspace slot and end there (the first
+// n_chunks items), or a whole row. Without items (the second launch): a split row, whose
+// summed chunks are in its first slot. Chunks share the launch of the whole rows so that
+// neither leaves the chip idle at its end: as a launch of their own, few chunks kept most
+// SIMDs waiting (23 chunks of 4096 ratings at D = 50 took 182 us).
 template <int DP, bool AUG, bool WT, bool BAYES, bool TS, bool STRIP = false>
-__global__ __launch_bounds__(64 * kRowWaves, 2) void k_rows(
-    const RowTask *__restrict__ rows, int64_t n_rows, const int32_t *__restrict__ idx,
+__global__ __launch_bounds__(64, 2) void k_rows(
+    const WorkItem *__restrict__ items, int64_t n_chunks, const RowTask *__restrict__ rows,
+    const int32_t *__restrict__ idx,
     const uint8_t *__restrict__ val, const float *__restrict__ wts,
     const float *__restrict__ Fp, int zrow,
-    const float *__restrict__ ws, int D, float lam, float *__restrict__ X_io,
+    float *__restrict__ ws, int D, float lam, float *__restrict__ X_io,
     double *__restrict__ sse_out,
     int32_t *__restrict__ flag_count, double *__restrict__ cyc_gram,
     double *__restrict__ cyc_solve, RowPrior pr, Hadamard hd) {
@@ -159,39 +148,53 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void k_rows(
   constexpr int T = C::T, NT = C::NT;
   constexpr int NPAN = DP / 4;
   // tile row I0 of the panel step, as published by each row group: [row group][tile column][lane column]
-  __shared__ floatx4 s_panel[kRowWaves][4][T][16];
+  __shared__ floatx4 panel[4][T][16];
   // per panel: M as a full 4 x 4 row-major block (zeros above the diagonal), then y_p
-  __shared__ __attribute__((aligned(16))) float s_ud[kRowWaves][NPAN][20];
-  __shared__ float s_dummy[kRowWaves][64];  // sink of the stores of lanes without an entry
-  __shared__ GroupStage s_stage[kRowWaves];        // gather staging of the row's rating groups
+  __shared__ __attribute__((aligned(16))) float ud[NPAN][20];
+  __shared__ float dummy[64];  // sink of the stores of lanes without an entry
+  __shared__ GroupStage s_stage;        // gather staging of the row's rating groups
 
-  const int wv = threadIdx.x >> 6;
-  const int64_t task = (int64_t)blockIdx.x * kRowWaves + wv;
-  if (task >= n_rows) return;
-  const RowTask rt = rows[task];
+  // one task per workgroup, whose record is then held in scalar registers
+  const int64_t task = blockIdx.x;
+  const bool summed = items == nullptr, chunk = task < n_chunks;
+  int64_t start = 0, slot;
+  int32_t row, deg;
+  if (summed) {
+    const RowTask rt = rows[task];
+    slot = rt.slot0;
+    row = rt.row;
+    deg = rt.deg;
+  } else {
+    const WorkItem it = items[task];
+    start = it.start;
+    slot = it.slot;
+    row = it.row;
+    deg = it.len;
+  }
   const int lane = threadIdx.x & 63, kq = lane >> 4, c = lane & 15;
-  floatx4(&panel)[4][T][16] = s_panel[wv];
-  float(&ud)[NPAN][20] = s_ud[wv];
-  float(&dummy)[64] = s_dummy[wv];
   const int aug_c = AUG ? aug_column<DP>(D) : -1;
 
   // A starts as lambda n_s I on the first D diagonal entries and I on the padding (only
   // the last tile holds padding); the Gram (or the sum of a split row's chunk partials)
   // is accumulated on top. With STRIP the last tile column starts from zero (it holds
   // strips during the Gram) and receives its initial value afterwards.
-  const float lam_n = (float)((double)lam * (double)rt.deg);
-  const float pscale = BAYES ? pr.scale_of(rt.row) : 1.f;
+  // A chunk starts from zero, and a split row's summed slot holds the initial value already.
+  const float lam_n = chunk ? 0.f : (float)((double)lam * (double)deg);
+  const float pad = chunk ? 0.f : 1.f;
+  const float pscale = chunk ? 0.f : BAYES ? pr.scale_of(row) : 1.f;
+  const float *__restrict__ sum_slot = ws + slot * (int64_t)slot_floats(DP);
+  const float *__restrict__ image = summed ? sum_slot : pr.init;
+  const float iscale = summed ? 1.f : pscale;
   auto tile_init = [&](int I, int J) -> floatx4 {
     if constexpr (BAYES) {
-      return pscale *
-             *reinterpret_cast<const floatx4 *>(pr.init + tidx<T>(I, J) * 256 + lane * 4);
+      return iscale * *reinterpret_cast<const floatx4 *>(image + tidx<T>(I, J) * 256 + lane * 4);
     } else {
       floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
       if (I == J) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int d = 16 * I + 4 * kq + r;
-          v[r] = c == 4 * kq + r ? ((I < T - 1 || d < D) ? lam_n : 1.f) : 0.f;
+          v[r] = c == 4 * kq + r ? ((I < T - 1 || d < D) ? lam_n : pad) : 0.f;
         }
       }
       return v;
@@ -208,8 +211,8 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void k_rows(
 #pragma unroll
   for (int X = 0; X < T; ++X) rhs[X] = 0.f;
 
-  float *__restrict__ xrow = X_io + (int64_t)rt.row * D;
-  if (rt.nslots == 0) {
+  float *__restrict__ xrow = X_io + (int64_t)row * D;
+  if (!summed) {
     float xo[T];
 #pragma unroll
     for (int X = 0; X < T; ++X) {
@@ -217,14 +220,13 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void k_rows(
       xo[X] = 16 * X + c < D ? v : 0.f;
     }
     double sse = 0.0;
-    const float *__restrict__ wp = WT ? wts + rt.start : nullptr;
-    const int32_t *__restrict__ tp = TS ? hd.idx2 + rt.start : nullptr;
-    const GroupLanes g0 =
-        first_group<WT, TS>(idx + rt.start, val + rt.start, wp, tp, rt.deg, zrow);
+    const float *__restrict__ wp = WT ? wts + start : nullptr;
+    const int32_t *__restrict__ tp = TS ? hd.idx2 + start : nullptr;
+    const GroupLanes g0 = first_group<WT, TS>(idx + start, val + start, wp, tp, deg, zrow);
     float no_corner = 0.f;
     gram_accumulate<DP, AUG && !STRIP, WT, TS, false, STRIP>(
-        acc, rhs, xo, sse, idx + rt.start, val + rt.start, wp, tp, rt.deg, Fp, hd.Tp, zrow,
-        STRIP ? -1 : aug_c, s_stage[wv], g0, no_corner, 0, 0);
+        acc, rhs, xo, sse, idx + start, val + start, wp, tp, deg, Fp, hd.Tp, zrow,
+        STRIP ? -1 : aug_c, s_stage, g0, no_corner, 0, 0);
     if constexpr (STRIP) strip_finish<DP>(acc, rhs, aug_c);
     if constexpr (!AUG) {
 #pragma unroll
@@ -235,22 +237,40 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void k_rows(
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sse += __shfl_xor(sse, o);
-    if (lane == 0 && rt.sse_idx >= 0) sse_out[rt.sse_idx] = sse;
-  } else {
-    const float *__restrict__ base = ws + rt.slot0 * (int64_t)slot_floats(DP);
-    for (int s = 0; s < rt.nslots; ++s) {
-      const float *__restrict__ sl = base + s * (int64_t)slot_floats(DP);
+    if (lane == 0) sse_out[task] = sse;
+    if (chunk) {
+      float *__restrict__ out = ws + slot * (int64_t)slot_floats(DP);
 #pragma unroll
-      for (int t = 0; t < NT; ++t) acc[t] += *reinterpret_cast<const floatx4 *>(sl + t * 256 + lane * 4);
+      for (int t = 0; t < NT; ++t)
+        *reinterpret_cast<floatx4 *>(out + t * 256 + lane * 4) = acc[t];
       if constexpr (!AUG) {
+        if (kq == 0) {
 #pragma unroll
-        for (int X = 0; X < T; ++X) rhs[X] += sl[NT * 256 + 16 * X + c];
+          for (int X = 0; X < T; ++X) out[NT * 256 + 16 * X + c] = rhs[X];
+        }
       }
+      if (cyc_gram != nullptr && lane == 0) {
+        cyc_gram[task] = (double)(__builtin_readcyclecounter() - t_start);
+        cyc_solve[task] = 0.0;
+      }
+      return;
+    }
+  } else {
+    if constexpr (!BAYES) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        acc[t] = *reinterpret_cast<const floatx4 *>(sum_slot + t * 256 + lane * 4);
+    }
+    if constexpr (!AUG) {
+#pragma unroll
+      for (int X = 0; X < T; ++X) rhs[X] = sum_slot[NT * 256 + 16 * X + c];
     }
   }
   if constexpr (STRIP) {
+    if (BAYES || !summed) {
 #pragma unroll
-    for (int I = 0; I < T; ++I) acc[tidx<T>(I, T - 1)] += tile_init(I, T - 1);
+      for (int I = 0; I < T; ++I) acc[tidx<T>(I, T - 1)] += tile_init(I, T - 1);
+    }
   }
   if constexpr (BAYES && !AUG) {
     // the prior's right-hand side (with the augmented column it sits in the tiles)
@@ -261,7 +281,7 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void k_rows(
     // the time chain's per-row right-hand side: into the augmented column (every row group
     // holds its own rows there) or into rhs (every lane holds the full sums)
     if (pr.h0 != nullptr) {
-      const float *__restrict__ hr = pr.h0 + (int64_t)rt.row * D;
+      const float *__restrict__ hr = pr.h0 + (int64_t)row * D;
       if constexpr (AUG) {
         if (c == aug_c) {
 #pragma unroll
@@ -465,7 +485,7 @@ __global__ __launch_bounds__(64 * kRowWaves, 2) void k_rows(
 
   if constexpr (BAYES) {
     // y += z / sqrt(alpha): the panels keep y_p in ud[p][16 .. 19]
-    const float *__restrict__ zr = pr.z + (int64_t)rt.row * D;
+    const float *__restrict__ zr = pr.z + (int64_t)row * D;
 #pragma unroll
     for (int d0 = 0; d0 < DP; d0 += 64) {
       const int d = d0 + lane;
@@ -595,13 +615,15 @@ static constexpr bool has_aug(int D) {
 }
 
 template <int DP, bool AUG, bool WT, bool BAYES, bool TS = false, bool STRIP = false>
-static void launch_rows_k(int64_t blocks, const RowTask *rows, int64_t n_rows,
+static void launch_rows_k(const WorkItem *items, int64_t n_chunks,
+                          const RowTask *rows, int64_t n_tasks,
                           const int32_t *idx, const uint8_t *val, const float *wts,
-                          const float *Fp, int zrow, const float *ws, int D, float lam, float *X,
+                          const float *Fp, int zrow, float *ws, int D, float lam, float *X,
                           double *sse, int32_t *flag, double *cyc_gram, double *cyc_solve,
                           const RowPrior &pr, const Hadamard &hd, hipStream_t s) {
-  hipLaunchKernelGGL((k_rows<DP, AUG, WT, BAYES, TS, STRIP>), dim3((unsigned)blocks),
-                     dim3(64 * kRowWaves), 0, s, rows, n_rows, idx, val, wts, Fp, zrow, ws, D,
+  hipLaunchKernelGGL((k_rows<DP, AUG, WT, BAYES, TS, STRIP>), dim3((unsigned)n_tasks),
+                     dim3(64), 0, s, items, n_chunks, rows, idx, val, wts, Fp,
+                     zrow, ws, D,
                      lam, X, sse, flag, cyc_gram, cyc_solve, pr, hd);
 }
 
@@ -615,15 +637,15 @@ static void launch_rows_aug(bool strip, A &&...args) {
 }
 
 template <int DP>
-static hipError_t launch_rows_t(const RowTask *rows, int64_t n_rows, const int32_t *idx,
+static hipError_t launch_rows_t(const WorkItem *items, int64_t n_chunks, const RowTask *rows,
+                                int64_t n_tasks, const int32_t *idx,
                                 const uint8_t *val, const float *wts, const float *Fp, int zrow,
-                                const float *ws, int D, float lam, float *X, double *sse,
+                                float *ws, int D, float lam, float *X, double *sse,
                                 int32_t *flag, double *cyc_gram, double *cyc_solve,
                                 const RowPrior &pr, const Hadamard &hd, hipStream_t s) {
-  if (n_rows <= 0) return hipSuccess;
-  const int64_t blocks = (n_rows + kRowWaves - 1) / kRowWaves;
+  if (n_tasks <= 0) return hipSuccess;
   const bool aug = has_aug<DP>(D), wt = wts != nullptr, strip = strip_width<DP>(D);
-#define ROW_ARGS blocks, rows, n_rows, idx, val, wts, Fp, zrow, ws, D, lam, X, sse, flag, \
+#define ROW_ARGS items, n_chunks, rows, n_tasks, idx, val, wts, Fp, zrow, ws, D, lam, X, sse, flag, \
                  cyc_gram, cyc_solve, pr, hd, s
   if (hd.idx2) {
     // tensor ALS (and its Gibbs draws): no weights; the tile form throughout (with the
@@ -657,49 +679,6 @@ static hipError_t launch_rows_t(const RowTask *rows, int64_t n_rows, const int32
   return hipGetLastError();
 }
 
-template <int DP, bool AUG, bool WT, bool TS = false, bool STRIP = false>
-static void launch_chunks_k(int64_t n, const WorkItem *items, const int32_t *idx,
-                            const uint8_t *val, const float *wts, const float *Fp, int zrow,
-                            const float *Xold, int D, float *ws, double *sse, const Hadamard &hd,
-                            hipStream_t s) {
-  hipLaunchKernelGGL((k_gram_chunks<DP, AUG, WT, TS, STRIP>), dim3((unsigned)n), dim3(64), 0, s,
-                     items, idx, val, wts, Fp, zrow, Xold, D, ws, sse, hd);
-}
-
-template <int DP, bool WT, bool TS, class... A>
-static void launch_chunks_aug(bool strip, A &&...args) {
-  if constexpr (DP >= 48 && DP <= 112) {
-    if (strip) return launch_chunks_k<DP, true, WT, TS, true>(args...);
-  }
-  launch_chunks_k<DP, true, WT, TS, false>(args...);
-}
-
-template <int DP>
-static hipError_t launch_chunks_t(const WorkItem *items, int64_t n, const int32_t *idx,
-                                  const uint8_t *val, const float *wts, const float *Fp,
-                                  int zrow, const float *Xold, int D, float *ws, double *sse,
-                                  const Hadamard &hd, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  const bool aug = has_aug<DP>(D), wt = wts != nullptr, strip = strip_width<DP>(D);
-#define CHUNK_ARGS n, items, idx, val, wts, Fp, zrow, Xold, D, ws, sse, hd, s
-  if (hd.idx2) {
-    if (wt) return hipErrorInvalidValue;
-    if (aug)
-      launch_chunks_k<DP, true, false, true>(CHUNK_ARGS);
-    else
-      launch_chunks_k<DP, false, false, true>(CHUNK_ARGS);
-  } else if (aug && wt)
-    launch_chunks_aug<DP, true, false>(strip, CHUNK_ARGS);
-  else if (aug)
-    launch_chunks_aug<DP, false, false>(strip, CHUNK_ARGS);
-  else if (wt)
-    launch_chunks_k<DP, false, true>(CHUNK_ARGS);
-  else
-    launch_chunks_k<DP, false, false>(CHUNK_ARGS);
-#undef CHUNK_ARGS
-  return hipGetLastError();
-}
-
 // Row kernels serve D > 20 (narrower widths take the one-lane solve).
 #define ALS_DP_SWITCH(dp, CALL)                 \
   switch (dp) {                                 \
@@ -713,24 +692,31 @@ static hipError_t launch_chunks_t(const WorkItem *items, int64_t n, const int32_
     default: return hipErrorInvalidValue;       \
   }
 
-hipError_t launch_rows(int dp, const RowTask *rows, int64_t n_rows, const int32_t *idx,
-                       const uint8_t *val, const float *wts, const float *Fp, int64_t n_fixed,
-                       const float *ws, int D, float lam, float *X, double *sse, int32_t *flag,
-                       double *cyc_gram, double *cyc_solve, const RowPrior &pr,
-                       const Hadamard &hd, hipStream_t s) {
+hipError_t launch_rows(int dp, const WorkItem *items, int64_t n_chunks, const RowTask *rows,
+                       int64_t n_tasks, const int32_t *idx, const uint8_t *val, const float *wts,
+                       const float *Fp, int64_t n_fixed, float *ws, int D, float lam, float *X,
+                       double *sse, int32_t *flag, double *cyc_gram, double *cyc_solve,
+                       const RowPrior &pr, const Hadamard &hd, hipStream_t s) {
   if ((cyc_gram == nullptr) != (cyc_solve == nullptr)) return hipErrorInvalidValue;
+  if ((items == nullptr) == (rows == nullptr) || (rows && n_chunks != 0))
+    return hipErrorInvalidValue;
   const int zrow = (int)n_fixed;
-  ALS_DP_SWITCH(dp, return launch_rows_t<DPV>(rows, n_rows, idx, val, wts, Fp, zrow, ws, D, lam,
-                                              X, sse, flag, cyc_gram, cyc_solve, pr, hd, s));
+  ALS_DP_SWITCH(dp, return launch_rows_t<DPV>(items, n_chunks, rows, n_tasks, idx, val, wts, Fp,
+                                              zrow, ws, D, lam, X, sse, flag, cyc_gram, cyc_solve,
+                                              pr, hd, s));
 }
 
-hipError_t launch_gram_chunks(int dp, const WorkItem *items, int64_t n, const int32_t *idx,
-                              const uint8_t *val, const float *wts, const float *Fp,
-                              int64_t n_fixed, const float *Xold, int D, float *ws, double *sse,
-                              const Hadamard &hd, hipStream_t s) {
-  const int zrow = (int)n_fixed;
-  ALS_DP_SWITCH(dp, return launch_chunks_t<DPV>(items, n, idx, val, wts, Fp, zrow, Xold, D, ws,
-                                                sse, hd, s));
+hipError_t launch_sum_slots(int dp, int D, const RowTask *rows, int64_t n_split, float lam,
+                            float *ws, const RowPrior &pr, hipStream_t s) {
+  if (n_split <= 0) return hipSuccess;
+  // with the augmented column a slot's right-hand side area is unused
+  const bool aug = ((D + 3) & ~3) < dp;
+  const int nq = (num_tiles(dp) * 256 + (aug ? 0 : dp)) / 4;
+  const int parts = (nq + 63) / 64;
+  if (n_split * parts > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_sum_slots, dim3((unsigned)(n_split * parts)), dim3(256), 0, s, rows,
+                     dp / 16, D, nq, parts, lam, ws, pr);
+  return hipGetLastError();
 }
 
 }  // namespace als

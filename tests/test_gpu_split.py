@@ -1,0 +1,67 @@
+"""The automatic split of long rows (no tuning given): rows at the edges of its threshold and
+chunks, slot counts with every remainder of the four summing waves, ALS and Gibbs draws with
+and without the augmented column; and a workspace too small for the fine split, which falls
+back to the coarse one instead of being refused.
+
+Bar: the half-sweep's own, relative row error 1e-4 against the fp64 oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import workload
+from tests.test_gpu_parity import check_first_half_sweeps, dev, rel_rows, ROW_TOL
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def edge_matrix(D):
+    """Users around multiples of the finest split's chunk (256 ratings up to D = 20, 512
+    above; rows of over two chunks split), among ordinary ones."""
+    c = 256 if D <= 20 else 512
+    N = 9 * c
+    deg = [2 * c - 1, 2 * c, 2 * c + 1, 3 * c - 1, 3 * c, 3 * c + 1, 4 * c, 4 * c + 1, 5 * c + 7,
+           8 * c, 8 * c + 64, 0, 1, 3 * c + 63] + [c // 4] * 50
+    ptr, col, val = workload.make_custom(len(deg), N, np.array(deg), seed=7 + D)
+    return len(deg), N, ptr, col, val, c, np.array(deg)
+
+
+@pytest.mark.parametrize("D", [1, 10, 16, 17, 20, 21, 32, 33, 48, 64, 100, 112, 128])
+def test_automatic_split(D):
+    from paper_1108_2580_amd import ALS
+
+    M, N, ptr, col, val, c, deg = edge_matrix(D)
+    U0, V0 = workload.init_factors(M, N, D, seed=5 + D)
+    with ALS(M, N, ptr, col, val, D) as als:
+        st = als.plan_stats("users")
+    assert st["split_rows"] == int((deg > 2 * c).sum())
+    assert st["chunks"] == int((-(-deg[deg > 2 * c] // c)).sum())
+    check_first_half_sweeps(M, N, ptr, col, val, D, 0.065, U0, V0, label=f"auto{D}")
+    # two slots fit: the plan takes the coarse split, under which no row here is split
+    with ALS(M, N, ptr, col, val, D, tuning=dict(workspace_bytes=2 * st["slot_bytes"])) as als:
+        assert als.plan_stats("users")["split_rows"] == 0
+    check_first_half_sweeps(M, N, ptr, col, val, D, 0.065, U0, V0, label=f"small{D}",
+                            tuning=dict(workspace_bytes=2 * st["slot_bytes"]))
+
+
+@pytest.mark.parametrize("D", [20, 33, 48, 100, 128])
+def test_gibbs_draw_of_split_rows(D):
+    from paper_1108_2580_amd import ALS
+
+    M, N, ptr, col, val, c, deg = edge_matrix(D)
+    U0, V0 = workload.init_factors(M, N, D, seed=9 + D)
+    rng = np.random.default_rng(D)
+    A = rng.normal(size=(D, D))
+    Lam, mu = A @ A.T / D + np.eye(D), rng.normal(size=D)
+    z = rng.standard_normal((M, D), dtype=np.float32)
+    d64 = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    alpha = 0.0625
+    print(f"gibbs split D={D}", flush=True)
+    with ALS(M, N, ptr, col, val, D) as als:
+        assert als.plan_stats("users")["split_rows"] > 0
+        out = dev(U0)
+        als.gibbs_half_sweep("users", dev(V0), alpha, d64(Lam), d64(mu), dev(z), out)
+        got = out.cpu().numpy()
+    want, _ = oracle.gibbs_rows(ptr, col, val.astype(np.float64), V0, alpha, Lam, mu, z, U0)
+    assert rel_rows(got, want).max() <= ROW_TOL
