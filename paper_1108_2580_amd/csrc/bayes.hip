@@ -20,7 +20,8 @@
 //                     beta0 n / beta* (mu0 - xbar)(mu0 - xbar)^T with S the scatter
 //                     about the mean), then Bartlett's draw: W* = F F^T, B lower
 //                     triangular with B_ii = sqrt(chi2_i) and normal B_ij, Lambda =
-//                     (F B)(F B)^T, and mu = mu0* + R^{-T} zmu with beta* Lambda = R R^T.
+//                     (F B)(F B)^T, and mu = mu0* + R^{-T} zmu with beta* Lambda = R R^T
+//                     (without forming W*, F or R: see the kernel).
 // The time chain of BPTF (T_0 ~ N(mu_T, Lambda_T^{-1}), T_k ~ N(T_{k-1}, Lambda_T^{-1})):
 //   k_time_rhs        a bin's prior right-hand side Lambda_T (m_k + [k < K - 1] T_{k+1}) /
 //                     alpha (m_k = mu_T for the first bin, else T_{k-1}) for the bins of
@@ -33,9 +34,8 @@
 //                     LDS, differences formed in fp64, exact for fp32 inputs), and
 //   k_time_steps_sum  the slices added in order; k_hyper_sample adds the result to
 //                     W*^{-1}.
-// The variates (chi-square, normals) are inputs. Matrices live as fp64
-// packed triangles in LDS (two of them, 132 KB at D = 128); the factorisations are
-// right-looking Cholesky steps with a barrier between steps.
+// The variates (chi-square, normals) are inputs. Matrices live in fp64 in registers and LDS
+// (133 KB at D = 128); the factorisations are right-looking steps with barriers between.
 #include "internal.h"
 
 namespace als {
@@ -76,19 +76,6 @@ __device__ void lds_cholesky(double *P, int D, int *bad) {
       const double lik = P[pl(i, k)];
       for (int j = k + 1 + (int)(threadIdx.x & 15); j <= i; j += 16)
         P[pl(i, j)] -= lik * P[pl(j, k)];
-    }
-  }
-  __syncthreads();
-}
-
-// Li = L^{-1} for the packed lower triangles L and Li (in LDS), one column per thread
-// (each column's forward substitution only reads L and its own earlier entries).
-__device__ void lds_lower_inverse(const double *L, double *Li, int D) {
-  for (int e = threadIdx.x; e < D; e += blockDim.x) {
-    for (int i = e; i < D; ++i) {
-      double s = i == e ? 1.0 : 0.0;
-      for (int m = e; m < i; ++m) s -= L[pl(i, m)] * Li[pl(m, e)];
-      Li[pl(i, e)] = s / L[pl(i, i)];
     }
   }
   __syncthreads();
@@ -316,106 +303,212 @@ __global__ __launch_bounds__(64) void k_hyper_reduce(const double *__restrict__ 
   seg_sums[(int64_t)seg * ne + q] = t;
 }
 
-// Normal-Wishart posterior and Bartlett draw on two packed triangles in LDS:
-//   P1 = W*^{-1} -> R (Cholesky);  P2 = R^{-1};  P1 = W* = R^{-T} R^{-1} -> F (Cholesky);
-//   P2 = F B (lower times lower is lower);  P1 = Lambda = (F B)(F B)^T, written out;
-//   P1 = beta* Lambda -> its Cholesky factor;  mu = mu0* + R^{-T} zmu.
+// 1 / sqrt(p) to about an ulp: the hardware estimate refined by Newton steps, each with about
+// a third of the dependent instructions of the exactly rounded square root and division.
+// Outside the range where p y y can neither overflow nor lose bits, those are used.
+__device__ __forceinline__ double rsqrt_f64(double p) {
+  if (!(p > 1e-280 && p < 1e280)) return 1.0 / sqrt(p);
+  double y = __builtin_amdgcn_rsq(p);
+#pragma unroll
+  for (int it = 0; it < 3; ++it) {
+    const double e = fma(-(p * y), y, 1.0);
+    y = fma(0.5 * y, e, y);
+  }
+  return y;
+}
+
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+// Normal-Wishart posterior and Bartlett draw in one workgroup of 32 x 32 threads. Thread
+// (ti, tj) holds the entries (ti + 32 a, tj + 32 b), b <= a, of the lower triangle in
+// registers; a step publishes one finished row through LDS, so it costs one barrier.
+//   W*^{-1} = G^T G (G lower, from the last row up), hence F = G^{-1} is the lower Cholesky
+//   factor of W* and needs no inverse and no second factorisation;
+//   G E = B, solved from the first row down, gives E = F B;
+//   Lambda = E E^T on fp64 MFMA (E staged square in LDS, zero above the diagonal);
+//   sqrt(beta*) E is the Cholesky factor R of beta* Lambda, so mu = mu0* + R^{-T} zmu is one
+//   back substitution.
+// Bound by the latency of the 2 D dependent steps (LDS round trip, reciprocal square root,
+// barrier): 106 us at D = 100 and 22 us at D = 20. Factoring W*^{-1}, inverting, multiplying
+// out W* and F B with one thread per row or column and factoring twice more took 1052 and
+// 67 us.
 // extra (nullable): a packed upper triangle added to W*^{-1} (the time chain's steps).
-__global__ __launch_bounds__(kBayesBlock) void k_hyper_sample(
+// A pivot of W*^{-1} or of beta* Lambda = R R^T that is not positive and finite sets *status.
+constexpr int kSampleThreads = 1024;
+constexpr int kSquare = kMaxD + 2;  // doubles per row: even, and odd in units of 16 bytes
+
+__global__ __launch_bounds__(kSampleThreads) void k_hyper_sample(
     const double *__restrict__ seg_sums, int64_t n, int D,
     const double *__restrict__ mu0, double beta0, const double *__restrict__ W0inv, double nu0,
     const double *__restrict__ chi2, const double *__restrict__ offd,
-    const double *__restrict__ zmu, const double *__restrict__ extra, double *__restrict__ H,
+    const double *__restrict__ zmu, const double *__restrict__ extra,
     double *__restrict__ mu_out, double *__restrict__ Lam_out, int32_t *__restrict__ status) {
-  __shared__ double P1[kPacked], P2[kPacked];
-  __shared__ double xbar[kMaxD], dv[kMaxD], tmp[kMaxD];
+  constexpr int NB = kMaxD / 32;
+  __shared__ double S[kMaxD * kSquare];  // the moments, then G, then E
+  __shared__ double buf[2][kMaxD];       // the row published by a step
+  __shared__ double xbar[kMaxD], dv[kMaxD], ginv[kMaxD];
   __shared__ int bad;
-  if (threadIdx.x == 0) bad = 0;
+  const int tid = threadIdx.x, ti = tid >> 5, tj = tid & 31;
   const int ne = D + D * (D + 1) / 2;
-  // the moments: segment sums added in segment order (H: global scratch of ne doubles)
-  for (int q = threadIdx.x; q < ne; q += blockDim.x) {
+  if (tid == 0) bad = 0;
+  if (tid < 2 * kMaxD) buf[tid / kMaxD][tid % kMaxD] = 0.0;
+  // the moments: segment sums added in segment order
+  for (int q = tid; q < ne; q += kSampleThreads) {
     double t = 0.0;
 #pragma unroll
     for (int g = 0; g < kReduceSegs; ++g) t += seg_sums[(int64_t)g * ne + q];
-    H[q] = t;
+    S[q] = t;
   }
   __syncthreads();
   const double nn = (double)n;
   const double beta_s = beta0 + nn;
   const double shrink = beta_s > 0.0 ? beta0 * nn / beta_s : 0.0;
-  for (int a = threadIdx.x; a < D; a += blockDim.x) {
-    xbar[a] = n > 0 ? H[a] / nn : 0.0;
-    dv[a] = mu0[a] - xbar[a];
+  if (tid < D) {
+    xbar[tid] = n > 0 ? S[tid] / nn : 0.0;
+    dv[tid] = mu0[tid] - xbar[tid];
   }
   __syncthreads();
   // W*^{-1} = W0^{-1} + (sum x x^T - n xbar xbar^T) + shrink dv dv^T (lower triangle)
-  for (int i = (int)(threadIdx.x >> 4); i < D; i += 16) {
-    for (int j = (int)(threadIdx.x & 15); j <= i; j += 16) {
-      const int q = j * D - j * (j - 1) / 2 + (i - j);
-      const double sxx = H[D + q];
-      P1[pl(i, j)] = W0inv[i * D + j] + (sxx - nn * xbar[i] * xbar[j]) + shrink * dv[i] * dv[j] +
-                     (extra ? extra[q] : 0.0);
+  double A[NB][NB];
+#pragma unroll
+  for (int a = 0; a < NB; ++a) {
+#pragma unroll
+    for (int b = 0; b <= a; ++b) {
+      const int i = ti + 32 * a, j = tj + 32 * b;
+      double v = 0.0;
+      if (i < D && j <= i) {
+        const int q = j * D - j * (j - 1) / 2 + (i - j);
+        v = W0inv[i * D + j] + (S[D + q] - nn * xbar[i] * xbar[j]) + shrink * dv[i] * dv[j] +
+            (extra ? extra[q] : 0.0);
+      }
+      A[a][b] = v;
     }
   }
-  __syncthreads();
-  for (int a = threadIdx.x; a < D; a += blockDim.x)
-    xbar[a] = (beta0 * mu0[a] + nn * xbar[a]) / beta_s;  // mu0*
-  lds_cholesky(P1, D, &bad);
-  lds_lower_inverse(P1, P2, D);
-  // W* = R^{-T} R^{-1}: entry (i, j), j <= i, sums over m >= i
-  for (int i = (int)(threadIdx.x >> 4); i < D; i += 16) {
-    for (int j = (int)(threadIdx.x & 15); j <= i; j += 16) {
-      double t = 0.0;
-      for (int m = i; m < D; ++m) t += P2[pl(m, i)] * P2[pl(m, j)];
-      P1[pl(i, j)] = t;
+  __syncthreads();  // S is rewritten row by row from here on
+  // W*^{-1} = G^T G: row k of G is row k of what the later rows leave, over its pivot's root
+#pragma unroll
+  for (int a = NB - 1; a >= 0; --a) {
+    if (32 * a >= D) continue;
+    for (int k = min(D, 32 * a + 32) - 1; k >= 32 * a; --k) {
+      double *row = buf[k & 1];
+      if (ti == k - 32 * a) {
+#pragma unroll
+        for (int b = 0; b <= a; ++b)
+          if (tj + 32 * b <= k) row[tj + 32 * b] = A[a][b];
+      }
+      __syncthreads();
+      double p = row[k];
+      const bool ok = p > 0.0 && isfinite(p);
+      if (!ok) p = 1.0;
+      const double rs = rsqrt_f64(p), inv = rs * rs;
+      // rows and columns from k on are finished: their registers no longer matter
+#pragma unroll
+      for (int c = 0; c <= a; ++c) {
+        const double f = row[ti + 32 * c] * inv;
+#pragma unroll
+        for (int b = 0; b <= c; ++b) A[c][b] = fma(-f, row[tj + 32 * b], A[c][b]);
+      }
+      if (tid <= k) S[k * kSquare + tid] = tid == k ? p * rs : row[tid] * rs;
+      if (tid == 0) {
+        ginv[k] = rs;
+        if (!ok) bad = 1;
+      }
     }
   }
-  lds_cholesky(P1, D, &bad);  // F
-  // Bartlett's B into P2 (packed in the same order: row m, column j < m: offd[pl(m, j) - m])
-  for (int q = threadIdx.x; q < D * (D + 1) / 2; q += blockDim.x) {
-    int m = (int)((sqrt(8.0 * q + 1.0) - 1.0) * 0.5);
-    while (pl(m, 0) > q) --m;
-    while (pl(m + 1, 0) <= q) ++m;
-    const int j = q - pl(m, 0);
-    P2[q] = j == m ? sqrt(chi2[m]) : offd[q - m];
-  }
-  __syncthreads();
-  // E = F B in place of F, one row per thread: entry (i, j) needs F[i][m] for m >= j only,
-  // so a row is overwritten in increasing j
-  for (int i = threadIdx.x; i < D; i += blockDim.x) {
-    for (int j = 0; j <= i; ++j) {
-      double t = 0.0;
-      for (int m = j; m <= i; ++m) t += P1[pl(i, m)] * P2[pl(m, j)];
-      P1[pl(i, j)] = t;
+  // G E = B with Bartlett's B (B_ii = sqrt(chi2_i), B_ij normal below)
+#pragma unroll
+  for (int a = 0; a < NB; ++a) {
+#pragma unroll
+    for (int b = 0; b <= a; ++b) {
+      const int i = ti + 32 * a, j = tj + 32 * b;
+      A[a][b] = i < D && j <= i ? (j == i ? sqrt(chi2[i]) : offd[i * (i - 1) / 2 + j]) : 0.0;
     }
   }
-  __syncthreads();
-  // Lambda = E E^T into P2
-  for (int i = (int)(threadIdx.x >> 4); i < D; i += 16) {
-    for (int j = (int)(threadIdx.x & 15); j <= i; j += 16) {
-      double t = 0.0;
-      for (int m = 0; m <= j; ++m) t += P1[pl(i, m)] * P1[pl(j, m)];
-      P2[pl(i, j)] = t;
-      Lam_out[i * D + j] = t;
-      Lam_out[j * D + i] = t;
+  __syncthreads();  // G and ginv are complete
+  bool fine = true;
+#pragma unroll
+  for (int a = 0; a < NB; ++a) {
+    for (int k = 32 * a; k < min(D, 32 * a + 32); ++k) {
+      double *row = buf[k & 1];
+      if (ti == k - 32 * a) {
+        const double r = ginv[k];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          const int j = tj + 32 * b;
+          const double e = b <= a && j <= k ? A[a][b <= a ? b : a] * r : 0.0;
+          // R's square in the entry, as a factorisation of beta* Lambda would meet it
+          const double e2 = e * e * beta_s;
+          fine = fine && isfinite(e2) && (j != k || (e > 0.0 && e2 > 0.0));
+          row[j] = e;
+        }
+      }
+      __syncthreads();
+      // rows up to k are finished; row k of G makes place for row k of E
+#pragma unroll
+      for (int c = a; c < NB; ++c) {
+        const double f = S[(ti + 32 * c) * kSquare + k];
+#pragma unroll
+        for (int b = 0; b <= a; ++b) A[c][b] = fma(-f, row[tj + 32 * b], A[c][b]);
+      }
+      if (tid < kMaxD) S[k * kSquare + tid] = row[tid];
     }
   }
+  if (!fine) bad = 1;
+  // rows past D, up to the 16-wide tiles of the product, are zero
+  const int T = (D + 15) / 16;
+  for (int q = tid; q < (16 * T - D) * kMaxD; q += kSampleThreads)
+    S[(D + q / kMaxD) * kSquare + q % kMaxD] = 0.0;
   __syncthreads();
-  for (int q = threadIdx.x; q < D * (D + 1) / 2; q += blockDim.x) P2[q] *= beta_s;
-  lds_cholesky(P2, D, &bad);
-  // mu = mu0* + R^{-T} zmu: back substitution with R^T, column by column (tmp holds the
-  // right-hand side still to be reduced)
-  for (int i = threadIdx.x; i < D; i += blockDim.x) tmp[i] = zmu[i];
-  for (int i = D - 1; i >= 0; --i) {
-    __syncthreads();
-    const double ti = tmp[i] / P2[pl(i, i)];
-    __syncthreads();
-    if (threadIdx.x == 0) tmp[i] = ti;
-    for (int m = threadIdx.x; m < i; m += blockDim.x) tmp[m] -= P2[pl(i, m)] * ti;
+  if (tid < 64) {
+    // mu = mu0* + R^{-T} zmu, R = sqrt(beta*) E: lane l holds the entries l and l + 64
+    const double sb = sqrt(beta_s);
+    double t[2], r[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int i = tid + 64 * h;
+      t[h] = i < D ? zmu[i] : 0.0;
+      r[h] = i < D ? 1.0 / (sb * S[i * kSquare + i]) : 0.0;
+    }
+#pragma unroll
+    for (int h = 1; h >= 0; --h) {
+      for (int i = min(D, 64 * h + 64) - 1; i >= 64 * h; --i) {
+        const double y = __shfl(t[h] * r[h], i - 64 * h);
+        if (tid == i - 64 * h) t[h] = y;
+#pragma unroll
+        for (int g = 0; g <= h; ++g)
+          if (tid + 64 * g < i) t[g] = fma(-(sb * S[i * kSquare + tid + 64 * g]), y, t[g]);
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int i = tid + 64 * h;
+      if (i < D) mu_out[i] = (beta0 * mu0[i] + nn * xbar[i]) / beta_s + t[h];
+    }
   }
-  __syncthreads();
-  for (int i = threadIdx.x; i < D; i += blockDim.x) mu_out[i] = xbar[i] + tmp[i];
-  if (threadIdx.x == 0) *status = bad ? 1 : 0;
+  // Lambda = E E^T: wave w takes the lower tiles w, w + 16, ...; lane (kq, c) supplies
+  // row c's entry 4 s + kq of both tile rows and receives rows 4 r + kq, column c
+  const int w = tid >> 6, lane = tid & 63, kq = lane >> 4, c = lane & 15;
+  for (int t = w; t < T * (T + 1) / 2; t += kSampleThreads / 64) {
+    int I = 0, J = t;
+    while (J > I) {
+      ++I;
+      J -= I;
+    }
+    const double *ra = S + (16 * I + c) * kSquare + kq, *rb = S + (16 * J + c) * kSquare + kq;
+    doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int s = 0; s < 4 * (J + 1); ++s)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ra[4 * s], rb[4 * s], acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * I + 4 * r + kq, j = 16 * J + c;
+      if (i < D && j <= i) {
+        Lam_out[i * D + j] = acc[r];
+        Lam_out[j * D + i] = acc[r];
+      }
+    }
+  }
+  if (tid == 0) *status = bad ? 1 : 0;
 }
 
 // Row a and column b (a <= b) of packed upper-triangle entry t (rows in order).
@@ -538,14 +631,14 @@ hipError_t launch_hyper_sample(const double *partials, int nblk, int64_t n, int 
                                hipStream_t s) {
   if (D < 1 || D > 128 || nblk < 1) return hipErrorInvalidValue;
   const int ne = hyper_entries(D);
-  double *seg_sums = scratch + ne + 8;
+  double *seg_sums = scratch;
   hipLaunchKernelGGL(k_hyper_reduce, dim3((unsigned)((ne + 63) / 64), kReduceSegs), dim3(64), 0, s,
                      partials, nblk, ne, seg_sums);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_hyper_sample, dim3(1), dim3(kBayesBlock), 0, s, seg_sums, n, D, mu0,
-                     beta0, W0inv, nu0, chi2, offd, zmu, (const double *)nullptr, scratch, mu_out,
-                     Lam_out, status);
+  hipLaunchKernelGGL(k_hyper_sample, dim3(1), dim3(kSampleThreads), 0, s, seg_sums, n, D, mu0,
+                     beta0, W0inv, nu0, chi2, offd, zmu, (const double *)nullptr, mu_out, Lam_out,
+                     status);
   return hipGetLastError();
 }
 
@@ -575,7 +668,7 @@ hipError_t launch_time_hyper(const float *T, int64_t K, int D, const double *mu0
                              double *Lam_out, int32_t *status, hipStream_t s) {
   if (D < 1 || D > 128 || K < 1) return hipErrorInvalidValue;
   const int ne = hyper_entries(D), ntri = D * (D + 1) / 2;
-  double *seg_sums = scratch + ne + 8;
+  double *seg_sums = scratch;
   hipLaunchKernelGGL(k_time_moments, dim3((unsigned)((kReduceSegs * ne + 255) / 256)), dim3(256),
                      0, s, T, D, seg_sums);
   hipError_t e = hipGetLastError();
@@ -590,9 +683,9 @@ hipError_t launch_time_hyper(const float *T, int64_t K, int D, const double *mu0
                      step_partials, (int)nblk, ntri, extra);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_hyper_sample, dim3(1), dim3(kBayesBlock), 0, s, seg_sums, (int64_t)1, D,
-                     mu0, beta0, W0inv, nu0, chi2, offd, zmu, (const double *)extra, scratch,
-                     mu_out, Lam_out, status);
+  hipLaunchKernelGGL(k_hyper_sample, dim3(1), dim3(kSampleThreads), 0, s, seg_sums, (int64_t)1, D,
+                     mu0, beta0, W0inv, nu0, chi2, offd, zmu, (const double *)extra, mu_out, Lam_out,
+                     status);
   return hipGetLastError();
 }
 

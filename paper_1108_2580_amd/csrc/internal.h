@@ -159,9 +159,8 @@ __host__ __device__ constexpr int tri(int a, int b) {  // a <= b
 
 // ---- Bayesian Gibbs step (bayes.hip) ----------------------------------------------------
 
-// fp64 scratch (doubles) of the hyperparameter draw: the summed moments and 16 segment
-// sums of them.
-inline size_t bayes_scratch_doubles(int D) { return (size_t)17 * (D + D * (D + 1) / 2) + 8; }
+// fp64 scratch (doubles) of the hyperparameter draw: 16 segment sums of the moments.
+inline size_t bayes_scratch_doubles(int D) { return (size_t)16 * (D + D * (D + 1) / 2); }
 // Floats of the prior image: a workspace slot (D > 20) or a packed record (D <= 20).
 inline size_t prior_init_floats(int D, int DP) {
   return lane_width(D) ? (size_t)ne_floats(lane_width(D)) : slot_floats_rt(DP);
