@@ -239,8 +239,8 @@ als_status als_holdout_rmse(als_ctx *ctx, const float *U, const float *V, double
  * Validation RMSE of (U, V) on caller-provided device pairs, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc): the same kernels and fixed summation order as als_holdout_rmse,
- * with no registration and no allocation. Its scratch (per-block sums, the reduction's
- * partials and the total) is a fixed array of 4 MiB in device memory that every GPU the
+ * with no registration and no allocation. Its scratch (per-block sums and the reduction's
+ * partials) is a fixed array of 4 MiB in device memory that every GPU the
  * library runs on holds until the process ends; the call neither allocates nor frees.
  *   users, items, ratings  device int32[n_pairs], int32[n_pairs], uint8[n_pairs], read only;
  *                          a pair with an index outside the tables makes the result NaN.

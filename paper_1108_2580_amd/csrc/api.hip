@@ -95,16 +95,16 @@ struct als_ctx {
   bool lane_solve = false;       // narrow D: Gram records + one row per lane solve
   double *d_sse_items = nullptr; // per chunk / row / piece squared residuals
   double *d_partials = nullptr;
-  double *d_sse_in = nullptr;    // entering-state SSE of the last half-sweep
-  double *d_sse_total = nullptr; // SSE of the last residual pass
   int32_t *d_flag = nullptr;
-  double *h_sse = nullptr;    // pinned
+  int32_t *d_ticket = nullptr;   // the reductions' block count
+  double *h_sse = nullptr;    // pinned, mapped: the SSE of the last residual or held-out pass
   double *h_sse_in = nullptr; // pinned, mapped [2]: the entering-state SSE of the last
                               // half-sweep, in one part, or two for the time chain's even and
                               // odd passes
   int sse_in_parts = 1;
   int32_t *h_flag = nullptr;  // pinned, mapped
-  double *hd_sse_in = nullptr; // device addresses of h_sse_in and h_flag
+  double *hd_sse = nullptr;    // device addresses of h_sse, h_sse_in and h_flag
+  double *hd_sse_in = nullptr;
   int32_t *hd_flag = nullptr;
   int last_side = -1;
   std::string err;
@@ -126,7 +126,6 @@ struct als_ctx {
   uint8_t *d_hr = nullptr;
   double *d_hold_blocks = nullptr; // per-block squared errors
   double *d_hold_partials = nullptr;
-  double *d_hold_sse = nullptr;
   // tensor ALS over time bins (als_set_time_bins)
   int32_t n_bins = 0;
   int32_t *d_tbin = nullptr;       // time bin of every rating, CSR order
@@ -379,7 +378,6 @@ void free_holdout(als_ctx *c) {
   dfree(c->d_hr);
   dfree(c->d_hold_blocks);
   dfree(c->d_hold_partials);
-  dfree(c->d_hold_sse);
   c->n_hold = -1;
 }
 
@@ -404,9 +402,8 @@ void free_ctx(als_ctx *c) {
   dfree(c->d_ne);
   dfree(c->d_sse_items);
   dfree(c->d_partials);
-  dfree(c->d_sse_in);
-  dfree(c->d_sse_total);
   dfree(c->d_flag);
+  dfree(c->d_ticket);
   if (c->h_sse) (void)hipHostFree(c->h_sse);
   if (c->h_sse_in) (void)hipHostFree(c->h_sse_in);
   if (c->h_flag) (void)hipHostFree(c->h_flag);
@@ -497,8 +494,8 @@ bool overlap(const void *a, size_t na, const void *b, size_t nb) {
   return pa < pb + nb && pb < pa + na;
 }
 
-// New-state residual pass over a side's pieces + fixed-order reduction into
-// d_sse_total; the fixed side must already be staged in d_fpad.
+// New-state residual pass over a side's pieces + fixed-order reduction into h_sse (read it
+// after the stream); the fixed side must already be staged in d_fpad.
 // n_fixed: the rows of the staged fixed side (d_fpad), whose next row is the zero row.
 als_status residual_pass(als_ctx *c, const SidePlan &P, const int32_t *idx, const uint8_t *val,
                          int64_t n_fixed, const float *X,
@@ -511,7 +508,7 @@ als_status residual_pass(als_ctx *c, const SidePlan &P, const int32_t *idx, cons
   }
   {
     PhaseTimer t(c, 4);
-    HIP_OR_FAIL(c, als::launch_reduce(c->d_sse_items, n, c->d_partials, c->d_sse_total,
+    HIP_OR_FAIL(c, als::launch_reduce(c->d_sse_items, n, c->d_partials, c->d_ticket, c->hd_sse,
                                       c->stream));
   }
   return ALS_OK;
@@ -519,7 +516,7 @@ als_status residual_pass(als_ctx *c, const SidePlan &P, const int32_t *idx, cons
 
 // ---- scratch of the allocation-free validation RMSE ---------------------------------------
 // als_pair_rmse_noalloc keeps the per-block squared errors of its pairs, the reduction's
-// partial sums and the total in this file-scope array: every GPU the library runs on holds
+// partial sums in this file-scope array: every GPU the library runs on holds
 // its own copy until the process ends. Host code never names the array itself (its name
 // on the host is only a stand-in); it uses the device address that hipGetSymbolAddress
 // returns for the current device, once per device, at context creation.
@@ -716,21 +713,23 @@ als_status als_create(als_ctx **out, int64_t n_users, int64_t n_items, int64_t n
   CK(dalloc(&c->d_fpad, (std::max(n_users, n_items) + 1) * (int64_t)c->DP));
   CK(dalloc(&c->d_sse_items, max_sse));
   CK(dalloc(&c->d_partials, als::reduce_partials(max_tasks)));
-  CK(dalloc(&c->d_sse_in, 1));
-  CK(dalloc(&c->d_sse_total, 1));
   CK(dalloc(&c->d_flag, 1));
-  CK(hipHostMalloc((void **)&c->h_sse, sizeof(double), hipHostMallocDefault));
-  // written by the half-sweep's last reduction kernel, so coherent and mapped
+  CK(dalloc(&c->d_ticket, 1));
+  // written by the reduction kernels, so coherent and mapped
+  CK(hipHostMalloc((void **)&c->h_sse, sizeof(double),
+                   hipHostMallocMapped | hipHostMallocCoherent));
   CK(hipHostMalloc((void **)&c->h_sse_in, 2 * sizeof(double),
                    hipHostMallocMapped | hipHostMallocCoherent));
   CK(hipHostMalloc((void **)&c->h_flag, sizeof(int32_t),
                    hipHostMallocMapped | hipHostMallocCoherent));
+  CK(hipHostGetDevicePointer((void **)&c->hd_sse, c->h_sse, 0));
   CK(hipHostGetDevicePointer((void **)&c->hd_sse_in, c->h_sse_in, 0));
   CK(hipHostGetDevicePointer((void **)&c->hd_flag, c->h_flag, 0));
   *c->h_flag = 0;
   *c->h_sse = 0.0;
   c->h_sse_in[0] = c->h_sse_in[1] = 0.0;
   CK(als::launch_fill_i32(c->d_flag, 1, 0, c->stream));
+  CK(als::launch_fill_i32(c->d_ticket, 1, 0, c->stream));
   CK(hipStreamSynchronize(c->stream));
 #undef CK
   *out = c;
@@ -753,7 +752,6 @@ struct SweepSpec {
   const float *wts = nullptr;
   int64_t n_fixed = 0;
   als::Hadamard hd;
-  bool keep_flags = false;  // add to the flag count of the previous sweep (time chain)
   int sse_in_part = 0;      // which part of the entering-state SSE this pass writes
 };
 
@@ -784,14 +782,15 @@ als_status half_sweep_impl(als_ctx *ctx, als_side side, const float *fixed_facto
   sp.n_fixed = n_fixed;
   {
     PhaseTimer t(ctx, 0);
-    HIP_OR_FAIL(ctx, als::launch_stage_fixed(fixed_factors, n_fixed, ctx->D, ctx->DP,
-                                             ctx->d_fpad, ctx->stream));
+    HIP_OR_FAIL(ctx, als::launch_stage_fixed(fixed_factors, n_fixed, ctx->d_fpad, nullptr, 0,
+                                             nullptr, ctx->D, ctx->DP, ctx->d_flag,
+                                             ctx->stream));
   }
   return run_sweep(ctx, sp, lambda, out_factors, rmse_out, pr);
 }
 
 // The batches of one half-sweep on an already staged fixed side (d_fpad, and d_fpad2 for
-// tensor ALS), the entering-state reduction, the flag count and, on request, the
+// tensor ALS; the staging launch clears the flag count), the entering-state reduction, the flag count and, on request, the
 // new-state RMSE.
 als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out_factors,
                      double *rmse_out, const als::RowPrior &pr) {
@@ -802,7 +801,6 @@ als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out
   const int64_t n_fixed = sp.n_fixed;
   const als::Hadamard &hd = sp.hd;
   const int side = sp.plan;
-  if (!sp.keep_flags) HIP_OR_FAIL(ctx, als::launch_fill_i32(ctx->d_flag, 1, 0, ctx->stream));
   for (const Batch &b : P.batches) {
     double *sse = ctx->d_sse_items + b.gitem_off;
     if (ctx->lane_solve) {
@@ -855,18 +853,19 @@ als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out
   {
     PhaseTimer t(ctx, 4);
     HIP_OR_FAIL(ctx, als::launch_reduce(ctx->d_sse_items, (int64_t)P.gitems.size(),
-                                        ctx->d_partials, ctx->d_sse_in, ctx->stream,
-                                        ctx->hd_sse_in + sp.sse_in_part, ctx->d_flag,
+                                        ctx->d_partials, ctx->d_ticket,
+                                        ctx->hd_sse_in + sp.sse_in_part, ctx->stream, ctx->d_flag,
                                         ctx->hd_flag));
   }
   ctx->last_side = side;
   ctx->sse_in_parts = sp.sse_in_part + 1;
   if (ctx->phase_timing && !ctx->lane_solve && !P.rows.empty() && side < 2) {
     const int64_t nr = cycle_tasks(P);
-    HIP_OR_FAIL(ctx, als::launch_reduce(ctx->d_cyc, nr, ctx->d_partials, ctx->d_cyc_sum,
+    HIP_OR_FAIL(ctx, als::launch_reduce(ctx->d_cyc, nr, ctx->d_partials, ctx->d_ticket,
+                                        ctx->d_cyc_sum,
                                         ctx->stream));
     HIP_OR_FAIL(ctx, als::launch_reduce(ctx->d_cyc + ctx->cyc_cap, nr, ctx->d_partials,
-                                        ctx->d_cyc_sum + 1, ctx->stream));
+                                        ctx->d_ticket, ctx->d_cyc_sum + 1, ctx->stream));
     HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_cyc_sum, ctx->d_cyc_sum, 2 * sizeof(double),
                                     hipMemcpyDeviceToHost, ctx->stream));
     HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream));
@@ -876,8 +875,6 @@ als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out
   if (rmse_out) {
     als_status st = residual_pass(ctx, P, idx, val, n_fixed, out_factors, hd);
     if (st != ALS_OK) return st;
-    HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_sse, ctx->d_sse_total, sizeof(double),
-                                    hipMemcpyDeviceToHost, ctx->stream));
     HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream));
     *rmse_out = ctx->nnz > 0 ? std::sqrt(*ctx->h_sse / (double)ctx->nnz) : 0.0;
     if (*ctx->h_flag > 0)
@@ -1061,13 +1058,11 @@ als_status als_rmse(als_ctx *ctx, const float *U, const float *V, double *rmse_o
   const SidePlan &P = ctx->plan[ALS_ROWS_USERS];
   {
     PhaseTimer t(ctx, 0);
-    HIP_OR_FAIL(ctx, als::launch_stage_fixed(V, ctx->N, ctx->D, ctx->DP, ctx->d_fpad,
-                                             ctx->stream));
+    HIP_OR_FAIL(ctx, als::launch_stage_fixed(V, ctx->N, ctx->d_fpad, nullptr, 0, nullptr, ctx->D,
+                                             ctx->DP, nullptr, ctx->stream));
   }
   als_status st = residual_pass(ctx, P, ctx->d_col, ctx->d_val, ctx->N, U);
   if (st != ALS_OK) return st;
-  HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_sse, ctx->d_sse_total, sizeof(double),
-                                  hipMemcpyDeviceToHost, ctx->stream));
   HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream));
   *rmse_out = ctx->nnz > 0 ? std::sqrt(*ctx->h_sse / (double)ctx->nnz) : 0.0;
   return ALS_OK;
@@ -1372,8 +1367,8 @@ als_status als_tensor_half_sweep(als_ctx *ctx, als_mode mode, float *U, float *V
   sp.hd.Tp = ctx->d_fpad2;
   {
     PhaseTimer t(ctx, 0);
-    HIP_OR_FAIL(ctx, als::launch_stage_fixed(F1, n1, ctx->D, ctx->DP, ctx->d_fpad, ctx->stream));
-    HIP_OR_FAIL(ctx, als::launch_stage_fixed(F2, n2, ctx->D, ctx->DP, ctx->d_fpad2, ctx->stream));
+    HIP_OR_FAIL(ctx, als::launch_stage_fixed(F1, n1, ctx->d_fpad, F2, n2, ctx->d_fpad2, ctx->D,
+                                             ctx->DP, ctx->d_flag, ctx->stream));
   }
   return run_sweep(ctx, sp, lambda, out, rmse_out, als::RowPrior{});
 }
@@ -1389,9 +1384,8 @@ als_status als_tensor_rmse(als_ctx *ctx, const float *U, const float *V, const f
   DeviceGuard g(ctx->device);
   {
     PhaseTimer t(ctx, 0);
-    HIP_OR_FAIL(ctx, als::launch_stage_fixed(V, ctx->N, ctx->D, ctx->DP, ctx->d_fpad, ctx->stream));
-    HIP_OR_FAIL(ctx, als::launch_stage_fixed(T, ctx->n_bins, ctx->D, ctx->DP, ctx->d_fpad2,
-                                             ctx->stream));
+    HIP_OR_FAIL(ctx, als::launch_stage_fixed(V, ctx->N, ctx->d_fpad, T, ctx->n_bins, ctx->d_fpad2,
+                                             ctx->D, ctx->DP, nullptr, ctx->stream));
   }
   als::Hadamard hd;
   hd.idx2 = ctx->d_tbin;
@@ -1399,8 +1393,6 @@ als_status als_tensor_rmse(als_ctx *ctx, const float *U, const float *V, const f
   als_status st = residual_pass(ctx, ctx->plan[ALS_ROWS_USERS], ctx->d_col, ctx->d_val, ctx->N,
                                 U, hd);
   if (st != ALS_OK) return st;
-  HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_sse, ctx->d_sse_total, sizeof(double),
-                                  hipMemcpyDeviceToHost, ctx->stream));
   HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream));
   *rmse_out = ctx->nnz > 0 ? std::sqrt(*ctx->h_sse / (double)ctx->nnz) : 0.0;
   return ALS_OK;
@@ -1453,8 +1445,8 @@ als_status als_tensor_gibbs_half_sweep(als_ctx *ctx, als_mode mode, float *U, fl
   sp.hd.Tp = ctx->d_fpad2;
   {
     PhaseTimer t(ctx, 0);
-    HIP_OR_FAIL(ctx, als::launch_stage_fixed(F1, n1, D, ctx->DP, ctx->d_fpad, ctx->stream));
-    HIP_OR_FAIL(ctx, als::launch_stage_fixed(F2, n2, D, ctx->DP, ctx->d_fpad2, ctx->stream));
+    HIP_OR_FAIL(ctx, als::launch_stage_fixed(F1, n1, ctx->d_fpad, F2, n2, ctx->d_fpad2, D,
+                                             ctx->DP, ctx->d_flag, ctx->stream));
   }
   als::RowPrior pr;
   pr.init = ctx->d_prior_init;
@@ -1494,7 +1486,6 @@ als_status als_tensor_gibbs_half_sweep(als_ctx *ctx, als_mode mode, float *U, fl
                                           ctx->d_time_h0, ctx->stream));
     SweepSpec sq = sp;
     sq.plan = 3 + parity;
-    sq.keep_flags = parity == 1;
     sq.sse_in_part = parity;
     st = run_sweep(ctx, sq, 0.f, T, nullptr, pr);
     if (st != ALS_OK) return st;
@@ -1624,7 +1615,6 @@ als_status als_set_holdout(als_ctx *ctx, int64_t n_pairs, const int32_t *users,
   if (e == hipSuccess) e = dalloc(&ctx->d_hr, n_pairs);
   if (e == hipSuccess) e = dalloc(&ctx->d_hold_blocks, nb);
   if (e == hipSuccess) e = dalloc(&ctx->d_hold_partials, als::reduce_partials(nb));
-  if (e == hipSuccess) e = dalloc(&ctx->d_hold_sse, 1);
   if (e == hipSuccess)
     e = hipMemcpy(ctx->d_hu, hu.data(), sizeof(int32_t) * n_pairs, hipMemcpyHostToDevice);
   if (e == hipSuccess)
@@ -1655,9 +1645,7 @@ als_status als_holdout_rmse(als_ctx *ctx, const float *U, const float *V, double
                                        ctx->d_hi, ctx->d_hr, nullptr, ctx->d_hold_blocks,
                                        ctx->stream));
   HIP_OR_FAIL(ctx, als::launch_reduce(ctx->d_hold_blocks, als::pair_blocks(ctx->n_hold, ctx->D),
-                                      ctx->d_hold_partials, ctx->d_hold_sse, ctx->stream));
-  HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_sse, ctx->d_hold_sse, sizeof(double),
-                                  hipMemcpyDeviceToHost, ctx->stream));
+                                      ctx->d_hold_partials, ctx->d_ticket, ctx->hd_sse, ctx->stream));
   HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream));
   *rmse_out = std::sqrt(*ctx->h_sse / (double)ctx->n_hold);
   return ALS_OK;
@@ -1681,19 +1669,17 @@ als_status als_pair_rmse_noalloc(als_ctx *ctx, const float *U, const float *V, i
     *rmse_out = 0.0;
     return ALS_OK;
   }
-  // scratch layout: per-block squared errors [nb], the reduction's partials [np], total [1]
+  // scratch layout: per-block squared errors [nb], the reduction's partials [np]
   const int64_t nb = als::pair_blocks(n_pairs, ctx->D);
   const int64_t np = als::reduce_partials(nb);
-  if (nb + np + 1 > kScratchDoubles)
+  if (nb + np > kScratchDoubles)
     return fail(ctx, ALS_ERR_INVALID_ARG, "%lld pairs need %lld scratch doubles, above %lld",
-                (long long)n_pairs, (long long)(nb + np + 1), (long long)kScratchDoubles);
+                (long long)n_pairs, (long long)(nb + np), (long long)kScratchDoubles);
   DeviceGuard g(ctx->device);
-  double *blocks = ctx->d_scratch, *partials = blocks + nb, *total = partials + np;
+  double *blocks = ctx->d_scratch, *partials = blocks + nb;
   HIP_OR_FAIL(ctx, als::launch_predict(U, V, ctx->M, ctx->N, ctx->D, n_pairs, users, items,
                                        ratings, nullptr, blocks, ctx->stream));
-  HIP_OR_FAIL(ctx, als::launch_reduce(blocks, nb, partials, total, ctx->stream));
-  HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_sse, total, sizeof(double), hipMemcpyDeviceToHost,
-                                  ctx->stream));
+  HIP_OR_FAIL(ctx, als::launch_reduce(blocks, nb, partials, ctx->d_ticket, ctx->hd_sse, ctx->stream));
   HIP_OR_FAIL(ctx, hipStreamSynchronize(ctx->stream));
   *rmse_out = std::sqrt(*ctx->h_sse / (double)n_pairs);
   return ALS_OK;

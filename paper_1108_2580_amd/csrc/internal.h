@@ -87,9 +87,11 @@ hipError_t launch_csc_permute_f32(const int64_t *row_ptr, const int32_t *col, co
                                   int64_t nblk, int32_t *scratch_cnt, int64_t *tot,
                                   const int64_t *col_ptr, float *w_t, hipStream_t s);
 
-// Copy of the fixed factors [n x D] into a zero-padded [(n + 1) x DP] buffer whose
-// row n is all zero (rowsolve.hip).
-hipError_t launch_stage_fixed(const float *F, int64_t n, int D, int DP, float *Fp, hipStream_t s);
+// Copies of the fixed factors into zero-padded buffers [(n + 1) x DP] whose row n is all zero
+// (rowsolve.hip): F [n x D] and, if F2 is given, a second table in the same launch. flag
+// (nullable): a device int32 set to zero, the half-sweep's count of flagged rows.
+hipError_t launch_stage_fixed(const float *F, int64_t n, float *Fp, const float *F2, int64_t n2,
+                              float *Fp2, int D, int DP, int32_t *flag, hipStream_t s);
 
 // Fused per-row normal equations, regularisation, Cholesky and solves; X is read
 // (entering state) and overwritten in place (rowsolve.hip). Exactly one of items and rows:
@@ -141,13 +143,14 @@ hipError_t launch_solve_lane(int D, const RowTask *rows, int64_t n_rows, int64_t
                              int64_t base, const float *ws, float *ne, float lam, float *X,
                              int32_t *flag, const RowPrior &pr, hipStream_t s);
 
-// Fixed-order sum of n doubles into *out; partials: double[reduce_partials(n)]. host_out, if
-// given, is the device address of mapped, coherent pinned host memory that receives the total
-// as well; flag and host_flag (both or neither) copy one device int32 to such memory.
+// Fixed-order sum of n doubles into *out (0 for n = 0); partials: double[reduce_partials(n)];
+// ticket: a device int32 that is zero before the first launch and that launches on one
+// stream may share. out may be the device address of mapped, coherent pinned host memory;
+// flag and host_flag (both or neither) copy one device int32 to such memory.
 int64_t reduce_partials(int64_t n);
-hipError_t launch_reduce(const double *v, int64_t n, double *partials, double *out,
-                         hipStream_t s, double *host_out = nullptr,
-                         const int32_t *flag = nullptr, int32_t *host_flag = nullptr);
+hipError_t launch_reduce(const double *v, int64_t n, double *partials, int32_t *ticket,
+                         double *out, hipStream_t s, const int32_t *flag = nullptr,
+                         int32_t *host_flag = nullptr);
 
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 

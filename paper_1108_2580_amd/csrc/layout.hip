@@ -15,7 +15,7 @@
 //              row the columns are distinct, so each rating claims the next
 //              position of its column with an integer atomic; a fence between
 //              rows keeps the claims of consecutive rows in row order.
-#include "internal.h"
+#include "gram.h"
 
 namespace als {
 
@@ -184,22 +184,29 @@ int64_t reduce_partials(int64_t n) {
   return n > 0 ? (n + per_blk - 1) / per_blk : 1;
 }
 
-__device__ __forceinline__ double block_tree_sum(double v, double *sh) {
-  sh[threadIdx.x] = v;
+// Sum over the block, in thread 0: a fixed order within each wave, then the waves in order.
+__device__ __forceinline__ double block_sum(double v, double *sh) {
+  v = sum_wave_f64(v);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int w = kRedBlock / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-    __syncthreads();
-  }
-  return sh[0];
+  double t = sh[0];
+#pragma unroll
+  for (int w = 1; w < kRedBlock / 64; ++w) t += sh[w];
+  return t;
 }
 
-// Block b sums v[b*2048 .. b*2048+2047]: thread t takes elements t, t+256, ...
-// in order, then a fixed tree over the threads.
-__global__ __launch_bounds__(kRedBlock) void k_reduce_partial(const double *__restrict__ v,
-                                                              int64_t n,
-                                                              double *__restrict__ partial) {
-  __shared__ double sh[kRedBlock];
+// Block b sums v[b*2048 .. b*2048+2047]: thread t takes elements t, t+256, ... in order, then
+// the threads in a fixed order. The block that finishes last adds the partial sums the same
+// way, whichever block it is, so the total does not depend on the order of the blocks; it
+// leaves the ticket at zero for the next launch. A second launch for the partial sums, and
+// copies of the total and the flag count to the host, cost about 5 us each.
+__global__ __launch_bounds__(kRedBlock) void k_reduce(const double *__restrict__ v, int64_t n,
+                                                      double *partial, int32_t *ticket,
+                                                      double *out,
+                                                      const int32_t *__restrict__ flag,
+                                                      int32_t *host_flag) {
+  __shared__ double sh[kRedBlock / 64];
+  __shared__ int s_last;
   const int64_t base = (int64_t)blockIdx.x * kRedBlock * kRedPer;
   double s = 0.0;
 #pragma unroll
@@ -207,42 +214,34 @@ __global__ __launch_bounds__(kRedBlock) void k_reduce_partial(const double *__re
     const int64_t i = base + threadIdx.x + (int64_t)m * kRedBlock;
     if (i < n) s += v[i];
   }
-  const double tot = block_tree_sum(s, sh);
-  if (threadIdx.x == 0) partial[blockIdx.x] = tot;
-}
-
-// One block: thread t sums partials t, t+256, ... in order, then a fixed tree. On request
-// thread 0 also stores the total, and a copy of *flag, into mapped host memory, in place of
-// two device-to-host copies after the kernel.
-__global__ __launch_bounds__(kRedBlock) void k_reduce_final(const double *__restrict__ partial,
-                                                            int64_t np, double *__restrict__ out,
-                                                            double *host_out,
-                                                            const int32_t *__restrict__ flag,
-                                                            int32_t *host_flag) {
-  __shared__ double sh[kRedBlock];
-  double s = 0.0;
-  for (int64_t i = threadIdx.x; i < np; i += kRedBlock) s += partial[i];
-  const double tot = block_tree_sum(s, sh);
+  double tot = block_sum(s, sh);
+  if (gridDim.x > 1) {
+    if (threadIdx.x == 0) {
+      __hip_atomic_store(&partial[blockIdx.x], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int done = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_ACQ_REL,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+      s_last = done == (int)gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    s = 0.0;
+    for (int64_t i = threadIdx.x; i < gridDim.x; i += kRedBlock)
+      s += __hip_atomic_load(&partial[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    tot = block_sum(s, sh);
+    if (threadIdx.x == 0)
+      __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   if (threadIdx.x == 0) {
     *out = tot;
-    if (host_out) *host_out = tot;
     if (host_flag) *host_flag = *flag;
   }
 }
 
-hipError_t launch_reduce(const double *v, int64_t n, double *partials, double *out,
-                         hipStream_t s, double *host_out, const int32_t *flag,
-                         int32_t *host_flag) {
+hipError_t launch_reduce(const double *v, int64_t n, double *partials, int32_t *ticket,
+                         double *out, hipStream_t s, const int32_t *flag, int32_t *host_flag) {
   if ((flag == nullptr) != (host_flag == nullptr)) return hipErrorInvalidValue;
-  const int64_t np = n > 0 ? reduce_partials(n) : 0;
-  if (n > 0) {
-    hipLaunchKernelGGL(k_reduce_partial, dim3((unsigned)np), dim3(kRedBlock), 0, s, v, n,
-                       partials);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kRedBlock), 0, s, partials, np, out, host_out,
-                     flag, host_flag);
+  hipLaunchKernelGGL(k_reduce, dim3((unsigned)reduce_partials(n)), dim3(kRedBlock), 0, s, v, n,
+                     partials, ticket, out, flag, host_flag);
   return hipGetLastError();
 }
 

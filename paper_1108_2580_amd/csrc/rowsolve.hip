@@ -28,19 +28,33 @@
 // (I, J), I <= J, holds A[16 I + 4 kq + r][16 J + c] in element r. The fixed
 // side is read from a staged copy with row stride DP (zero padded), so every
 // gathered row starts on a 64-byte boundary.
+#include <algorithm>
+
 #include "gram.h"
 
 namespace als {
 
 // Copy the fixed factors [n x D] into a zero-padded [(n + 1) x DP] buffer whose
 // last row is all zero (the stand-in of absent ratings). Thread (q, y) of a block
-// writes float4 q of staged row blockIdx.x * blockDim.y + y (grid-stride over rows).
-__global__ void k_stage_fixed(const float *__restrict__ F, int64_t n, int D, int DP,
-                              float *__restrict__ Fp) {
+// writes float4 q of staged row b * blockDim.y + y (stride over rows). The first blocks1
+// blocks take the first table, the others the second; block 0 clears the flag count.
+struct StageTable {
+  const float *F;
+  int64_t n;
+  float *Fp;
+};
+__global__ void k_stage_fixed(StageTable t1, StageTable t2, int blocks1, int D, int DP,
+                              int32_t *__restrict__ flag) {
+  const bool first = (int)blockIdx.x < blocks1;
+  const float *__restrict__ F = first ? t1.F : t2.F;
+  float *__restrict__ Fp = first ? t1.Fp : t2.Fp;
+  const int64_t n = first ? t1.n : t2.n;
+  const int64_t b = first ? blockIdx.x : blockIdx.x - blocks1;
+  const int64_t blocks = first ? blocks1 : gridDim.x - blocks1;
   const int q = threadIdx.x;
   const int d0 = 4 * q;
-  for (int64_t row = (int64_t)blockIdx.x * blockDim.y + threadIdx.y; row <= n;
-       row += (int64_t)gridDim.x * blockDim.y) {
+  if (flag && blockIdx.x == 0 && threadIdx.x == 0 && threadIdx.y == 0) *flag = 0;
+  for (int64_t row = b * blockDim.y + threadIdx.y; row <= n; row += blocks * blockDim.y) {
     float v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[k] = (row < n && d0 + k < D) ? F[row * D + d0 + k] : 0.f;
@@ -48,14 +62,17 @@ __global__ void k_stage_fixed(const float *__restrict__ F, int64_t n, int D, int
   }
 }
 
-hipError_t launch_stage_fixed(const float *F, int64_t n, int D, int DP, float *Fp, hipStream_t s) {
-  if (n < 0 || DP % 4 != 0 || DP / 4 > 256) return hipErrorInvalidValue;
+hipError_t launch_stage_fixed(const float *F, int64_t n, float *Fp, const float *F2, int64_t n2,
+                              float *Fp2, int D, int DP, int32_t *flag, hipStream_t s) {
+  if (n < 0 || n2 < 0 || DP % 4 != 0 || DP / 4 > 256) return hipErrorInvalidValue;
   const int dp4 = DP / 4;
   const int rows_per_block = 256 / dp4;
-  int64_t blocks = (n + 1 + rows_per_block - 1) / rows_per_block;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(k_stage_fixed, dim3((unsigned)blocks), dim3(dp4, rows_per_block), 0, s, F, n,
-                     D, DP, Fp);
+  auto blocks_of = [&](int64_t rows) {
+    return std::min<int64_t>((rows + 1 + rows_per_block - 1) / rows_per_block, 65536);
+  };
+  const int64_t b1 = blocks_of(n), b2 = F2 ? blocks_of(n2) : 0;
+  hipLaunchKernelGGL(k_stage_fixed, dim3((unsigned)(b1 + b2)), dim3(dp4, rows_per_block), 0, s,
+                     StageTable{F, n, Fp}, StageTable{F2, n2, Fp2}, (int)b1, D, DP, flag);
   return hipGetLastError();
 }
 
