@@ -221,7 +221,7 @@ void csc_blocking(int64_t n_users, int64_t n_items, int64_t &rows_per_blk, int64
 // Wavefronts that the Gram kernel of a width keeps on a SIMD.
 int gram_waves(const als_ctx *ctx) {
   if (ctx->lane_solve) return 6;
-  return ctx->DP <= 32 ? 4 : ctx->DP <= 48 ? 3 : 2;
+  return ctx->DP <= 64 ? 5 : ctx->DP <= 80 ? 4 : ctx->DP <= 112 ? 3 : 2;
 }
 
 // Split of the long rows where the caller leaves it open. The longest item must be short

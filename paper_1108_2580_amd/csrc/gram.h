@@ -135,8 +135,11 @@ template <int DP>
 struct RowCfg {
   static constexpr int T = DP / 16;
   static constexpr int NT = T * (T + 1) / 2;
-  // steps per gathered block (wide rows keep two blocks in flight)
-  static constexpr int STEPS = T <= 2 ? 16 : (T <= 4 ? 8 : (T <= 6 ? 4 : 2));
+  // steps per gathered block. Wide rows keep two blocks of one step (four ratings) in flight:
+  // blocks of eight to two steps hid no more latency beside the other waves and took the
+  // registers of one of them (at eight tiles they spilled: tensor ALS, D = 128, 10.7 against
+  // 8.3 ms)
+  static constexpr int STEPS = T <= 2 ? 16 : 1;
 };
 
 template <int V>
@@ -282,8 +285,8 @@ __device__ __forceinline__ void gather_block(float (&a)[STEPS][DP / 16], float (
   }
 }
 
-// MFMA Gram update, right-hand side and per-step partial predictions of the gathered
-// steps s0 .. s0 + STEPS - 1, in sub-blocks of up to four steps; sub-blocks past the
+// MFMA Gram update, right-hand side and per-step partial predictions (handed to put(step,
+// value)) of the gathered steps s0 .. s0 + STEPS - 1, in sub-blocks of up to four steps; sub-blocks past the
 // item's last step (steps of this group) are skipped. With AUG the right-hand side is
 // a column of the Gram and rhs is left alone. With WT (weighted ALS) the first MFMA
 // operand carries c f, so the tiles accumulate sum c f f^T (and, in the augmented
@@ -304,10 +307,10 @@ __device__ __forceinline__ void gather_block(float (&a)[STEPS][DP / 16], float (
 // of the last tile (sb), for rating kq alone; acc[tidx(I, T - 1)] then holds these
 // per-rating strips until strip_finish sums and rearranges them.
 template <int DP, int STEPS, bool AUG, bool WT, bool CORNER = false, bool STRIP = false,
-          bool CMFMA = false>
+          bool CMFMA = false, class Put>
 __device__ __forceinline__ void mma_block(floatx4 (&acc)[RowCfg<DP>::NT],
                                           float (&rhs)[DP / 16], const float (&xo)[DP / 16],
-                                          float (&pi)[16], const float (&a)[STEPS][DP / 16],
+                                          Put put, const float (&a)[STEPS][DP / 16],
                                           const float (&sb)[STEPS], const float (&r)[STEPS],
                                           const float (&wt)[STEPS], int s0, int steps,
                                           float &corner, int cx, int cy) {
@@ -326,13 +329,14 @@ __device__ __forceinline__ void mma_block(floatx4 (&acc)[RowCfg<DP>::NT],
 #pragma unroll
       for (int u = u0; u < u0 + SUB; ++u) {
         const float rw = WT ? wt[u] * r[u] : r[u];
-        float wa[T];
+        float wa[T], p = 0.f;
 #pragma unroll
         for (int X = 0; X < T; ++X) {
           wa[X] = WT ? wt[u] * a[u][X] : a[u][X];
           if constexpr (!AUG) rhs[X] = fmaf(rw, a[u][X], rhs[X]);
-          pi[s0 + u] = fmaf(a[u][X], xo[X], pi[s0 + u]);
+          p = fmaf(a[u][X], xo[X], p);
         }
+        put(s0 + u, p);
         // the two-tile strip leaves the augmented column out: features 0..15 take their
         // right-hand side on VALU (16..19 take it in the corner products)
         if constexpr (STRIP2) rhs[0] = fmaf(rw, a[u][0], rhs[0]);
@@ -367,17 +371,21 @@ __device__ __forceinline__ void mma_block(floatx4 (&acc)[RowCfg<DP>::NT],
   }
 }
 
-// End of a 64-rating group: every lane stores its 16 step partials (feature lane c's
-// share of the predictions of steps 0..15 of its rating group) to LDS, then lane (kq, c)
-// sums the 16 feature lanes' shares of step c in lane order, which gives the full
-// prediction of rating g + 4 c + kq; its squared residual is added to sse.
-__device__ __forceinline__ void group_residuals(const float (&pi)[16], GroupStage &st, int buf,
-                                                int g, int n, double &sse) {
+// Where a lane's share of step s's predictions goes in the group's LDS area.
+__device__ __forceinline__ float *step_partials(GroupStage &st) {
+  const int lane = threadIdx.x & 63;
+  return &st.red[(lane >> 4) * kRedGroup + (lane & 15) * kRedRow];
+}
+
+// End of a 64-rating group, whose 16 step partials every lane has stored to LDS (feature lane
+// c's share of the predictions of steps 0..15 of its rating group): lane (kq, c) sums the 16
+// feature lanes' shares of step c in lane order, which gives the full prediction of rating
+// g + 4 c + kq; its squared residual is added to sse. Shares of steps past the item's end may
+// be stale; their sums are dropped.
+__device__ __forceinline__ void group_residuals(GroupStage &st, int buf, int g, int n,
+                                                double &sse) {
   const int lane = threadIdx.x & 63;
   const int kq = lane >> 4, c = lane & 15;
-  float *row = &st.red[kq * kRedGroup + c * kRedRow];
-#pragma unroll
-  for (int u = 0; u < 16; ++u) row[u] = pi[u];
   wave_sync();
   const float *col = &st.red[kq * kRedGroup + c];
   float p = col[0];
@@ -442,11 +450,15 @@ __device__ __forceinline__ void gram_accumulate(floatx4 (&acc)[RowCfg<DP>::NT],
           float a[STEPS][T];
           float sb[STEPS], r[STEPS], w[STEPS];
           gather_block<DP, STEPS, AUG, WT, TS>(a, sb, r, w, st, 0, s0, Fp, Tp, aug_lane);
-          mma_block<DP, STEPS, AUG, WT, CORNER, STRIP, CORNER && !TS>(acc, rhs, xo, pi, a, sb, r, w, s0, steps,
+          auto put = [&](int step, float p) { pi[step] = p; };
+          mma_block<DP, STEPS, AUG, WT, CORNER, STRIP, CORNER && !TS>(acc, rhs, xo, put, a, sb, r, w, s0, steps,
                                                        corner, cx, cy);
         }
       }
-      group_residuals(pi, st, 0, g, n, sse);
+      float *const red = step_partials(st);
+#pragma unroll
+      for (int u = 0; u < 16; ++u) red[u] = pi[u];
+      group_residuals(st, 0, g, n, sse);
       wave_sync();  // the buffer is restaged by the next group
       gv = gn;
     }
@@ -462,9 +474,9 @@ __device__ __forceinline__ void gram_accumulate(floatx4 (&acc)[RowCfg<DP>::NT],
       const GroupLanes gn = group_lanes<WT, TS>(ip, vp, wp, tp, n, g + 64, zrow);
       const int steps = min(16, (n - g + 3) >> 2);
       __builtin_assume(steps >= 1);  // g < n: the group's first step always exists
-      float pi[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) pi[u] = 0.f;
+      // the partials go to LDS step by step: held to the group's end they took 16 registers
+      float *const red = step_partials(st);
+      auto put = [&](int step, float p) { red[step] = p; };
       auto block = [&](auto bc) {
         constexpr int b = decltype(bc)::value;
         constexpr int s0 = b * STEPS;
@@ -472,7 +484,7 @@ __device__ __forceinline__ void gram_accumulate(floatx4 (&acc)[RowCfg<DP>::NT],
           if constexpr (b + 1 < NB)
             gather_block<DP, STEPS, AUG, WT, TS, STRIP>(a1, b1, r1, w1, st, buf, s0 + STEPS, Fp,
                                                         Tp, aug_lane);
-          mma_block<DP, STEPS, AUG, WT, CORNER, STRIP, CORNER && !TS>(acc, rhs, xo, pi, a0, b0, r0, w0, s0,
+          mma_block<DP, STEPS, AUG, WT, CORNER, STRIP, CORNER && !TS>(acc, rhs, xo, put, a0, b0, r0, w0, s0,
                                                        steps, corner, cx, cy);
         } else {
           if constexpr (b + 1 < NB) {
@@ -485,12 +497,12 @@ __device__ __forceinline__ void gram_accumulate(floatx4 (&acc)[RowCfg<DP>::NT],
             gather_block<DP, STEPS, AUG, WT, TS, STRIP>(a0, b0, r0, w0, st, buf ^ 1, 0, Fp, Tp,
                                                         aug_lane);
           }
-          mma_block<DP, STEPS, AUG, WT, CORNER, STRIP, CORNER && !TS>(acc, rhs, xo, pi, a1, b1, r1, w1, s0,
+          mma_block<DP, STEPS, AUG, WT, CORNER, STRIP, CORNER && !TS>(acc, rhs, xo, put, a1, b1, r1, w1, s0,
                                                        steps, corner, cx, cy);
         }
       };
       unroll_blocks<0, NB>(block);
-      group_residuals(pi, st, buf, g, n, sse);
+      group_residuals(st, buf, g, n, sse);
       buf ^= 1;
     }
   }

@@ -46,15 +46,15 @@ __global__ __launch_bounds__(64) void k_resid(const WorkItem *__restrict__ items
     wave_sync();
     float a[16][T], sb[16], r[16], w[16];
     gather_block<DP, 16, false, false, TS>(a, sb, r, w, st, 0, 0, Fp, hd.Tp, false);
-    float pi[16];
+    float *const red = step_partials(st);
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       float t = 0.f;
 #pragma unroll
       for (int Xt = 0; Xt < T; ++Xt) t = fmaf(a[u][Xt], xo[Xt], t);
-      pi[u] = t;
+      red[u] = t;
     }
-    group_residuals(pi, st, 0, g, n, sse);
+    group_residuals(st, 0, g, n, sse);
     wave_sync();  // the buffer is restaged by the next group
     gv = gn;
   }

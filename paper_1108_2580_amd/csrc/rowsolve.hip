@@ -126,10 +126,21 @@ __global__ __launch_bounds__(256) void k_sum_slots(const RowTask *__restrict__ r
   *p = v;
 }
 
-// Two wavefronts per SIMD (the second launch bound) outweigh the few registers the
-// wide widths then spill: the accumulator tiles move to arch VGPRs and the gather
-// latency of one row hides behind the other row's MFMAs.
-//
+// Wavefronts per SIMD that the register allocation aims at. The factorisation is a chain of
+// dependent steps, so a SIMD needs several rows' chains at once; one step per gathered block
+// and the step partials in LDS leave room for them. Measured on 10M lognormal ratings, us per
+// sweep at two (three for 48 tiles' width) waves and now: D = 36 843 and 770, 50 1424 and
+// 1227, 64 1604 and 1512, 68 2049 and 1785, 92 2960 and 2690, 100 3600 and 3405 (where 41
+// registers spill). At eight tiles the accumulators alone take 144 of the 168 registers that
+// three waves leave (1127 spills); with an explicit right-hand side and the prior image the
+// bound spills around a hundred.
+template <int DP, bool AUG, bool BAYES>
+constexpr int kRowWaves = BAYES && !AUG              ? 2
+                          : DP == 64                 ? 5
+                          : DP == 80                 ? 4
+                          : DP == 96 || DP == 112    ? 3
+                                                     : 2;
+
 // Panel step (rows p0 .. p0 + 3, held by row group g of tile row I0):
 //   the 4x4 diagonal block A_gg = U_gg^T U_gg is factored in every lane and
 //   M = U_gg^{-T} formed explicitly (10 entries); lane (kq, c) then forms the panel
@@ -151,7 +162,7 @@ __global__ __launch_bounds__(256) void k_sum_slots(const RowTask *__restrict__ r
 // neither leaves the chip idle at its end: as a launch of their own, few chunks kept most
 // SIMDs waiting (23 chunks of 4096 ratings at D = 50 took 182 us).
 template <int DP, bool AUG, bool WT, bool BAYES, bool TS, bool STRIP = false>
-__global__ __launch_bounds__(64, 2) void k_rows(
+__global__ __launch_bounds__(64, (kRowWaves<DP, AUG, BAYES>)) void k_rows(
     const WorkItem *__restrict__ items, int64_t n_chunks, const RowTask *__restrict__ rows,
     const int32_t *__restrict__ idx,
     const uint8_t *__restrict__ val, const float *__restrict__ wts,
@@ -164,12 +175,27 @@ __global__ __launch_bounds__(64, 2) void k_rows(
   using C = RowCfg<DP>;
   constexpr int T = C::T, NT = C::NT;
   constexpr int NPAN = DP / 4;
-  // tile row I0 of the panel step, as published by each row group: [row group][tile column][lane column]
-  __shared__ floatx4 panel[4][T][16];
-  // per panel: M as a full 4 x 4 row-major block (zeros above the diagonal), then y_p
-  __shared__ __attribute__((aligned(16))) float ud[NPAN][20];
-  __shared__ float dummy[64];  // sink of the stores of lanes without an entry
-  __shared__ GroupStage s_stage;        // gather staging of the row's rating groups
+  // LDS of the factorisation: tile row I0 of the panel step, as published by each row group
+  // [row group][tile column][lane column]; per panel, M as a full 4 x 4 row-major block (zeros
+  // above the diagonal), then y_p; a sink for the stores of lanes without an entry. Up to
+  // seven tiles it takes turns with the gather's staging in one piece (6.4 to 9.6 KB a wave),
+  // so that LDS does not limit the waves per SIMD; eight tiles run two waves, and there the
+  // wait between the turns only costs (0.5 %).
+  constexpr bool kTurns = T <= 7;
+  constexpr int kPanelBytes = 4 * T * 16 * 16, kUdBytes = NPAN * 80;
+  constexpr int kTurnBytes = kPanelBytes + kUdBytes + 256;
+  constexpr int kStageBytes = sizeof(GroupStage);
+  __shared__ __attribute__((aligned(16))) char
+      s_turns[!kTurns ? 16 : kTurnBytes > kStageBytes ? kTurnBytes : kStageBytes];
+  __shared__ __attribute__((aligned(16))) char s_panel[kTurns ? 16 : kPanelBytes];
+  __shared__ __attribute__((aligned(16))) char s_ud[kTurns ? 16 : kUdBytes];
+  __shared__ __attribute__((aligned(16))) char s_dummy[kTurns ? 16 : 256];
+  __shared__ __attribute__((aligned(16))) char s_own[kTurns ? 16 : kStageBytes];
+  GroupStage &s_stage = *reinterpret_cast<GroupStage *>(kTurns ? s_turns : s_own);
+  auto &panel = *reinterpret_cast<floatx4(*)[4][T][16]>(kTurns ? s_turns : s_panel);
+  auto &ud = *reinterpret_cast<float(*)[NPAN][20]>(kTurns ? s_turns + kPanelBytes : s_ud);
+  auto &dummy =
+      *reinterpret_cast<float(*)[64]>(kTurns ? s_turns + kPanelBytes + kUdBytes : s_dummy);
 
   // one task per workgroup, whose record is then held in scalar registers
   const int64_t task = blockIdx.x;
@@ -319,6 +345,7 @@ __global__ __launch_bounds__(64, 2) void k_rows(
   }
 
   const uint64_t t_gram = __builtin_readcyclecounter();
+  if constexpr (kTurns) wave_sync();  // the panels overwrite the gather's staging
 
   // ---- factorisation A = U^T U with forward substitution U^T y = b ------------------------
   // Panel step (I0, g) of rows p0 .. p0 + 3, p0 = 16 I0 + 4 g. Its update of the trailing
