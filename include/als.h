@@ -69,7 +69,7 @@ typedef enum {
  * finer split (down to 512 and 256). */
 typedef struct {
   int32_t hub_threshold;   /* rows with more ratings are split into chunks (default 8192) */
-  int32_t chunk;           /* ratings per chunk of a split row (default 4096) */
+  int32_t chunk;           /* ratings per chunk of a split row (default at most 4096) */
   int64_t workspace_bytes; /* cap on the partial-Gram workspace; larger half-sweeps run in
                               several batches (default 48 GiB) */
 } als_tuning;

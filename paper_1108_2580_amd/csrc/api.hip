@@ -32,6 +32,12 @@ namespace {
 // ones (auto_split).
 constexpr int32_t kMaxChunk = 4096;
 constexpr int32_t kMinChunk = 256;
+// Chunks cut along windows of a large fixed table (Split).
+constexpr int64_t kWindowBytes = 4 << 20;  // one XCD's L2
+constexpr int64_t kMinWindows = 6;
+constexpr int64_t kMaxWindows = 64;
+constexpr int64_t kMinWindowChunk = 128;
+constexpr int64_t kXcds = 8;
 constexpr int64_t kDefaultWorkspace = 48LL << 30;
 // cap on the block-by-column count table of the device transpose
 constexpr int64_t kCscTableEntries = 1LL << 29;
@@ -246,10 +252,34 @@ void auto_split(const als_ctx *ctx, int64_t ratings, int64_t &hub, int64_t &chun
   hub = 2 * c;
 }
 
+// How rows are split: those of over hub ratings into chunks of at most chunk ratings. With
+// windows (D <= 20, whose gather is bound by memory) a chunk also stays within about one
+// window of the fixed table (indices ascend within a row), and order_chunks runs the chunks
+// of one window together on one XCD, so that their rows come from its L2 instead of from
+// beyond (the item side of 263M ratings at D = 20 moved 31 GB a half-sweep at 7.2 TB/s). Us
+// per sweep without and with windows of 4 MB: 128 MB table, 263M ratings 7807 and 7038 (2 MB:
+// 7059); 64 MB, 100M 3007 and 2793; 64 MB at D = 10, 150M 4236 and 3619; 51 MB, 30M 1222 and
+// 1158; 32 MB, 60M 1572 and 1495. A 13 MB table gains nothing (345 and 344; BPTF 1197 and
+// 1211), hence kMinWindows. Splitting rows from 4096 or 2048 ratings on as well gained no more
+// (7102, 7118): their chunks' records cost what the hits save.
+struct Split {
+  int64_t hub = 0, chunk = 0, windows = 1;
+  int64_t chunk_of(int64_t d) const {
+    if (windows <= 1) return chunk;
+    return std::min(chunk, std::max<int64_t>(kMinWindowChunk, (d / windows + 63) / 64 * 64));
+  }
+  int64_t chunks_of(int64_t d) const {
+    return d > hub ? (d + chunk_of(d) - 1) / chunk_of(d) : 0;
+  }
+};
+
+als_status order_chunks(als_ctx *ctx, SidePlan &P, const int32_t *d_idx, int64_t n_fixed);
+
 // parity >= 0: only the rows s with s % 2 == parity, and those without ratings are
 // scheduled like the others (the time chain's bins, whose prior depends on the row).
+// d_idx: the side's fixed-row indices on the device; n_fixed: rows of the table they index.
 als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr,
-                      int parity = -1) {
+                      const int32_t *d_idx, int64_t n_fixed, int parity = -1) {
   const int64_t n_rows = (int64_t)ptr.size() - 1;
   P = SidePlan();
   P.n_rows = n_rows;
@@ -273,12 +303,24 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
     return ptr[a + 1] - ptr[a] > ptr[b + 1] - ptr[b];
   });
   P.rows_with = (int64_t)order.size();
-  int64_t hub = ctx->tune.hub_threshold, chunk = ctx->tune.chunk;
-  if (!hub && !chunk) auto_split(ctx, ratings, hub, chunk);
-  if (!hub) hub = 2 * kMaxChunk;
-  if (!chunk) chunk = kMaxChunk;
   const int64_t cap = std::max<int64_t>(1, ctx->tune.workspace_bytes / (int64_t)slot_bytes_of(ctx));
-  const int64_t max_chunks = P.max_deg > hub ? (P.max_deg + chunk - 1) / chunk : 0;
+  Split sp;
+  sp.hub = ctx->tune.hub_threshold;
+  sp.chunk = ctx->tune.chunk;
+  if (!sp.hub && !sp.chunk) {
+    auto_split(ctx, ratings, sp.hub, sp.chunk);
+    if (ctx->lane_solve) {
+      sp.windows = n_fixed * ctx->DP * 4 / kWindowBytes;
+      if (sp.windows < kMinWindows) sp.windows = 1;
+      sp.windows = std::min(sp.windows, kMaxWindows);
+      int64_t slots = 0;
+      for (int32_t s : order) slots += sp.chunks_of(ptr[s + 1] - ptr[s]);
+      if (slots > cap) sp.windows = 1;
+    }
+  }
+  if (!sp.hub) sp.hub = 2 * kMaxChunk;
+  if (!sp.chunk) sp.chunk = kMaxChunk;
+  const int64_t max_chunks = sp.chunks_of(P.max_deg);
   if (max_chunks > cap)
     return fail(ctx, ALS_ERR_INVALID_ARG,
                 "workspace of %lld bytes holds %lld slots; a split row needs %lld",
@@ -288,8 +330,7 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
   {
     int64_t first = 0, slots = 0;
     for (int64_t k = 0; k < (int64_t)order.size(); ++k) {
-      const int64_t d = ptr[order[k] + 1] - ptr[order[k]];
-      const int64_t nch = d > hub ? (d + chunk - 1) / chunk : 0;
+      const int64_t nch = sp.chunks_of(ptr[order[k] + 1] - ptr[order[k]]);
       if (slots + nch > cap) {
         spans.push_back({first, k});
         first = k;
@@ -299,14 +340,14 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
     }
     if (first < (int64_t)order.size()) spans.push_back({first, (int64_t)order.size()});
   }
-  for (const auto &sp : spans) {
+  for (const auto &span : spans) {
     Batch b{(int64_t)P.gitems.size(), 0, 0, (int64_t)P.rows.size(), 0, 0, P.split_rows, 0};
     // chunks of the batch's split rows
-    for (int64_t k = sp.first; k < sp.second; ++k) {
+    for (int64_t k = span.first; k < span.second; ++k) {
       const int32_t s = order[k];
       const int64_t d = ptr[s + 1] - ptr[s];
-      if (d <= hub) continue;
-      const int64_t nch = (d + chunk - 1) / chunk;
+      if (d <= sp.hub) continue;
+      const int64_t nch = sp.chunks_of(d), chunk = sp.chunk_of(d);
       ++P.split_rows;
       RowTask rt;
       rt.slot0 = b.n_slots;
@@ -327,10 +368,10 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
       b.n_split += 1;
     }
     // unsplit rows, one gather item each
-    for (int64_t k = sp.first; k < sp.second; ++k) {
+    for (int64_t k = span.first; k < span.second; ++k) {
       const int32_t s = order[k];
       const int64_t d = ptr[s + 1] - ptr[s];
-      if (d > hub) continue;
+      if (d > sp.hub) continue;
       RowTask rt;
       rt.slot0 = (int64_t)P.rows.size();  // record of the row's packed normal equations
       rt.row = s;
@@ -362,6 +403,48 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
   if (!P.rows.empty())
     HIP_OR_FAIL(ctx, hipMemcpy(P.d_rows, P.rows.data(), sizeof(RowTask) * P.rows.size(),
                                hipMemcpyHostToDevice));
+  if (sp.windows > 1 && P.n_chunks > 0) return order_chunks(ctx, P, d_idx, n_fixed);
+  return ALS_OK;
+}
+
+// Order of each batch's chunks by the part of the fixed table that they read: the chunks,
+// sorted by their first index, are cut into kXcds equal runs, and the runs are interleaved, so
+// that the chunks in flight on one XCD (workgroups go to the XCDs in turn) read one window of
+// the table that its L2 can hold.
+als_status order_chunks(als_ctx *ctx, SidePlan &P, const int32_t *d_idx, int64_t n_fixed) {
+  const int64_t n = (int64_t)P.gitems.size();
+  std::vector<int32_t> first(n);
+  int32_t *d_first = nullptr;
+  hipError_t e = dalloc(&d_first, n);
+  if (e == hipSuccess) e = als::launch_first_index(P.d_gitems, n, d_idx, d_first, ctx->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+  if (e == hipSuccess)
+    e = hipMemcpy(first.data(), d_first, sizeof(int32_t) * n, hipMemcpyDeviceToHost);
+  dfree(d_first);
+  HIP_OR_FAIL(ctx, e);
+  constexpr int64_t kBuckets = 4096;
+  for (const Batch &b : P.batches) {
+    if (b.n_gchunks == 0) continue;
+    // a stable counting sort over the table's buckets
+    const WorkItem *src = P.gitems.data() + b.gitem_off;
+    const int32_t *key = first.data() + b.gitem_off;
+    std::vector<int64_t> at(kBuckets + 1, 0);
+    auto bucket = [&](int64_t q) { return (int64_t)key[q] * kBuckets / std::max<int64_t>(n_fixed, 1); };
+    for (int64_t q = 0; q < b.n_gchunks; ++q) at[bucket(q) + 1] += 1;
+    for (int64_t k = 0; k < kBuckets; ++k) at[k + 1] += at[k];
+    std::vector<WorkItem> out(b.n_gchunks);
+    const int64_t per = (b.n_gchunks + kXcds - 1) / kXcds, full = b.n_gchunks - (per - 1) * kXcds;
+    for (int64_t q = 0; q < b.n_gchunks; ++q) {
+      // rank r belongs to run x: the first `full` runs have per chunks, the others per - 1
+      const int64_t r = at[bucket(q)]++;
+      const int64_t x = r < full * per ? r / per : full + (r - full * per) / std::max<int64_t>(per - 1, 1);
+      const int64_t k = r < full * per ? r % per : (r - full * per) % std::max<int64_t>(per - 1, 1);
+      out[k * kXcds + x] = src[q];
+    }
+    std::copy(out.begin(), out.end(), P.gitems.begin() + b.gitem_off);
+    HIP_OR_FAIL(ctx, hipMemcpy(P.d_gitems + b.gitem_off, out.data(),
+                               sizeof(WorkItem) * b.n_gchunks, hipMemcpyHostToDevice));
+  }
   return ALS_OK;
 }
 
@@ -695,9 +778,9 @@ als_status als_create(als_ctx **out, int64_t n_users, int64_t n_items, int64_t n
     return bail(ALS_ERR_HIP);
   }
   // ---- A3: schedules ----
-  als_status st = build_plan(c, c->plan[ALS_ROWS_USERS], c->h_row_ptr);
+  als_status st = build_plan(c, c->plan[ALS_ROWS_USERS], c->h_row_ptr, c->d_col, n_items);
   if (st != ALS_OK) return bail(st);
-  st = build_plan(c, c->plan[ALS_ROWS_ITEMS], c->h_col_ptr);
+  st = build_plan(c, c->plan[ALS_ROWS_ITEMS], c->h_col_ptr, c->d_row_idx, n_users);
   if (st != ALS_OK) return bail(st);
   int64_t max_slots = 0, max_sse = 0, max_rows = 0, max_tasks = 0;
   for (auto &P : c->plan) {
@@ -1291,9 +1374,9 @@ als_status als_set_time_bins(als_ctx *ctx, int32_t n_bins, const int32_t *bins) 
     HIP_OR_FAIL(ctx, e);
     HIP_OR_FAIL(ctx, e2);
   }
-  als_status st = build_plan(ctx, TP, ptr);
-  if (st == ALS_OK) st = build_plan(ctx, ctx->plan[3], ptr, 0);
-  if (st == ALS_OK) st = build_plan(ctx, ctx->plan[4], ptr, 1);
+  als_status st = build_plan(ctx, TP, ptr, ctx->d_tb_user, ctx->M);
+  if (st == ALS_OK) st = build_plan(ctx, ctx->plan[3], ptr, ctx->d_tb_user, ctx->M, 0);
+  if (st == ALS_OK) st = build_plan(ctx, ctx->plan[4], ptr, ctx->d_tb_user, ctx->M, 1);
   if (st != ALS_OK) return st;
   // shared buffers sized for the time-bin plans too
   int64_t max_slots = 0, max_sse = 0, max_rows = 0, max_tasks = 0;

@@ -87,6 +87,10 @@ hipError_t launch_csc_permute_f32(const int64_t *row_ptr, const int32_t *col, co
                                   int64_t nblk, int32_t *scratch_cnt, int64_t *tot,
                                   const int64_t *col_ptr, float *w_t, hipStream_t s);
 
+// First index of each gather item (layout.hip).
+hipError_t launch_first_index(const WorkItem *items, int64_t n, const int32_t *idx,
+                              int32_t *first, hipStream_t s);
+
 // Copies of the fixed factors into zero-padded buffers [(n + 1) x DP] whose row n is all zero
 // (rowsolve.hip): F [n x D] and, if F2 is given, a second table in the same launch. flag
 // (nullable): a device int32 set to zero, the half-sweep's count of flagged rows.

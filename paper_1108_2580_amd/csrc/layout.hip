@@ -174,6 +174,22 @@ hipError_t launch_csc_permute_f32(const int64_t *row_ptr, const int32_t *col, co
   return hipGetLastError();
 }
 
+// first[i] = the first index of gather item i (0 for an item without ratings).
+__global__ __launch_bounds__(256) void k_first_index(const WorkItem *__restrict__ items, int64_t n,
+                                                     const int32_t *__restrict__ idx,
+                                                     int32_t *__restrict__ first) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) first[i] = items[i].len > 0 ? idx[items[i].start] : 0;
+}
+
+hipError_t launch_first_index(const WorkItem *items, int64_t n, const int32_t *idx,
+                              int32_t *first, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_first_index, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, items, n,
+                     idx, first);
+  return hipGetLastError();
+}
+
 // ---- fixed-order reduction of doubles --------------------------------------------------
 
 constexpr int kRedBlock = 256;

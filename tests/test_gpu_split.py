@@ -1,7 +1,8 @@
 """The automatic split of long rows (no tuning given): rows at the edges of its threshold and
 chunks, slot counts with every remainder of the four summing waves, ALS and Gibbs draws with
-and without the augmented column; and a workspace too small for the fine split, which falls
-back to the coarse one instead of being refused.
+and without the augmented column; a workspace too small for the fine split, which falls back
+to the coarse one instead of being refused; and chunks cut and ordered by windows of a large
+fixed table.
 
 Bar: the half-sweep's own, relative row error 1e-4 against the fp64 oracle."""
 import numpy as np
@@ -65,3 +66,25 @@ def test_gibbs_draw_of_split_rows(D):
         got = out.cpu().numpy()
     want, _ = oracle.gibbs_rows(ptr, col, val.astype(np.float64), V0, alpha, Lam, mu, z, U0)
     assert rel_rows(got, want).max() <= ROW_TOL
+
+
+@pytest.mark.parametrize("D,M", [(10, 450_000), (20, 250_000)])
+def test_windowed_chunks(D, M):
+    """The items' fixed table is over 24 MB: the long items' chunks follow windows of it, the
+    users' side keeps the plain split."""
+    from paper_1108_2580_amd import ALS
+
+    N = 60
+    deg = np.full(M, 3)
+    deg[::50] = 0
+    deg[7] = N
+    ptr, col, val = workload.make_custom(M, N, deg, seed=11 + D,
+                                         item_weights=np.r_[1.0 / np.arange(1, N), 0.0])
+    U0, V0 = workload.init_factors(M, N, D, seed=13 + D)
+    with ALS(M, N, ptr, col, val, D) as als:
+        st, whole = als.plan_stats("items"), als.plan_stats("users")
+    d = np.bincount(col, minlength=N)
+    assert whole["split_rows"] == 0 and st["split_rows"] == int((d > 512).sum()) > 10
+    assert st["chunks"] <= int((-(-d // 128))[d > 512].sum())
+    assert st["chunks"] >= int((-(-d // 256))[d > 512].sum())
+    check_first_half_sweeps(M, N, ptr, col, val, D, 0.065, U0, V0, label=f"windows{D}")
