@@ -205,7 +205,7 @@ als_status als_get_phase_cycles(als_ctx *ctx, als_side side, double *gram_cycles
 /*
  * Held-out prediction (paper Sec. 2.2: a prediction is the dot product of the user's
  * and the item's vector) for n_pairs (user, item) pairs:
- *   pred[p] = U[users[p], :] . V[items[p], :]   (fp32, features summed in order).
+ *   pred[p] = U[users[p], :] . V[items[p], :]   (fp32, summed in a fixed order).
  *   U, V          device fp32 [n_users x D], [n_items x D], 16-byte aligned.
  *   users, items  device int32[n_pairs]; a pair with an index outside the tables gets
  *                 pred = NaN and reads nothing.

@@ -2,13 +2,12 @@
 // the validation RMSE (Sec. 4.1), for a list of (user, item) pairs.
 //
 // The work is two gathered D-vectors and one dot product per pair, so it is
-// bound by memory. Narrow or unaligned rows: one lane takes one whole pair and
-// reads both rows with the widest loads their alignment allows (float4 when
-// D % 4 == 0, then float2, then float), eight vectors per row in flight before
-// any arithmetic. Rows of 16 floats and more (D % 4 == 0): a group of 4 or 8
-// lanes shares a pair, so that each load instruction reads contiguous row
-// segments (the wave's 64 lanes touch 16 or 8 rows instead of 64), and the
-// group's partial sums are added by shuffles. The dot
+// bound by memory. Rows are read with the widest loads that every row's alignment
+// allows (float4 when D % 4 == 0, then float2, then float). A group of 4 or 8 lanes
+// shares a pair, so that each load instruction reads contiguous row segments (the
+// wave's 64 lanes touch 16 or 8 rows instead of 64), and the group's partial sums are
+// added by shuffles; rows of fewer than four loads take one lane per pair, eight
+// vectors per row in flight before any arithmetic. The dot
 // product runs with fused multiply-adds in fp32 (in feature order for one lane per
 // pair; strided per lane, then a shuffle tree, for a group). Pairs whose
 // indices fall outside the factor tables give NaN and read nothing. With
@@ -19,6 +18,18 @@
 namespace als {
 
 namespace {
+
+// Floats per load: the widest that every row's alignment allows (16-byte aligned tables).
+int predict_vec(int D) { return D % 4 == 0 ? 4 : D % 2 == 0 ? 2 : 1; }
+
+// Lanes per pair: eight from 24 loads a row on, four from four, else one (float4 loads measured
+// on the full-size workload's pairs: D = 20 0.106 ms with one lane and 0.072 with four, D = 100
+// 0.735 and, with eight, 0.250). Us for 3M pairs with one lane and grouped: D = 5 39 and 32, 10
+// 50 and 40, 13 111 and 42, 33 318 and 83, 50 286 and 105, 89 932 and 128, 127 1360 and 173.
+int predict_group(int D) {
+  const int nv = D / predict_vec(D);
+  return nv >= 24 ? 8 : (nv >= 4 ? 4 : 1);
+}
 
 constexpr int kPairBlock = 256;
 constexpr int kVecInFlight = 8;
@@ -70,10 +81,10 @@ __device__ __forceinline__ float row_dot(const float *__restrict__ u, const floa
   return acc;
 }
 
-// G lanes share a pair (G a power of two, 1 < G <= 16, D % 4 == 0): lane g of the group
+// G lanes share a pair (G a power of two, 1 < G <= 16, D % VW == 0): lane g of the group
 // loads vectors g, g + G, ... of both rows, so that one load instruction of the wave reads
 // whole contiguous row segments; the G partial sums are then added across the group.
-template <int G, bool SSE>
+template <int VW, int G, bool SSE>
 __global__ __launch_bounds__(kPairBlock) void k_predict_group(
     const float *__restrict__ U, const float *__restrict__ V, int64_t M, int64_t N, int D,
     int64_t n, const int32_t *__restrict__ users, const int32_t *__restrict__ items,
@@ -89,12 +100,13 @@ __global__ __launch_bounds__(kPairBlock) void k_predict_group(
     rv = SSE ? (double)r[p] : 0.0;
     ok = ((uint64_t)u < (uint64_t)M) & ((uint64_t)i < (uint64_t)N);
     if (ok) {
-      const float4 *__restrict__ a = reinterpret_cast<const float4 *>(U + (int64_t)u * D);
-      const float4 *__restrict__ b = reinterpret_cast<const float4 *>(V + (int64_t)i * D);
-      const int nv = D / 4;
+      using T = typename Vec<VW>::T;
+      const T *__restrict__ a = reinterpret_cast<const T *>(U + (int64_t)u * D);
+      const T *__restrict__ b = reinterpret_cast<const T *>(V + (int64_t)i * D);
+      const int nv = D / VW;
       constexpr int kIn = 4;  // vectors of each row in flight per lane
       for (int c0 = g; c0 < nv; c0 += kIn * G) {
-        float4 x[kIn], y[kIn];
+        T x[kIn], y[kIn];
 #pragma unroll
         for (int k = 0; k < kIn; ++k) {
           if (c0 + k * G < nv) {
@@ -104,7 +116,7 @@ __global__ __launch_bounds__(kPairBlock) void k_predict_group(
         }
 #pragma unroll
         for (int k = 0; k < kIn; ++k)
-          if (c0 + k * G < nv) acc = Vec<4>::fma_dot(x[k], y[k], acc);
+          if (c0 + k * G < nv) acc = Vec<VW>::fma_dot(x[k], y[k], acc);
       }
     }
   }
@@ -169,18 +181,18 @@ __global__ __launch_bounds__(kPairBlock) void k_predict(
   }
 }
 
-template <int G>
+template <int VW, int G>
 hipError_t launch_predict_group(const float *U, const float *V, int64_t M, int64_t N, int D,
                                 int64_t n, const int32_t *users, const int32_t *items,
                                 const uint8_t *r, float *pred, double *sse_blocks,
                                 hipStream_t s) {
   const unsigned blocks = (unsigned)pair_blocks(n, D);
   if (sse_blocks)
-    hipLaunchKernelGGL((k_predict_group<G, true>), dim3(blocks), dim3(kPairBlock), 0, s, U, V, M,
-                       N, D, n, users, items, r, pred, sse_blocks);
+    hipLaunchKernelGGL((k_predict_group<VW, G, true>), dim3(blocks), dim3(kPairBlock), 0, s, U, V,
+                       M, N, D, n, users, items, r, pred, sse_blocks);
   else
-    hipLaunchKernelGGL((k_predict_group<G, false>), dim3(blocks), dim3(kPairBlock), 0, s, U, V, M,
-                       N, D, n, users, items, r, pred, sse_blocks);
+    hipLaunchKernelGGL((k_predict_group<VW, G, false>), dim3(blocks), dim3(kPairBlock), 0, s, U,
+                       V, M, N, D, n, users, items, r, pred, sse_blocks);
   return hipGetLastError();
 }
 
@@ -188,6 +200,11 @@ template <int VW>
 hipError_t launch_predict_vw(const float *U, const float *V, int64_t M, int64_t N, int D,
                              int64_t n, const int32_t *users, const int32_t *items,
                              const uint8_t *r, float *pred, double *sse_blocks, hipStream_t s) {
+  const int G = predict_group(D);
+  if (G == 8)
+    return launch_predict_group<VW, 8>(U, V, M, N, D, n, users, items, r, pred, sse_blocks, s);
+  if (G == 4)
+    return launch_predict_group<VW, 4>(U, V, M, N, D, n, users, items, r, pred, sse_blocks, s);
   const unsigned blocks = (unsigned)pair_blocks(n, D);
   if (sse_blocks)
     hipLaunchKernelGGL((k_predict<VW, true>), dim3(blocks), dim3(kPairBlock), 0, s, U, V, M, N, D,
@@ -200,14 +217,6 @@ hipError_t launch_predict_vw(const float *U, const float *V, int64_t M, int64_t 
 
 }  // namespace
 
-// Lanes per pair (measured on the full-size workload's pairs): rows of 96 floats and
-// more (multiples of 4) take 8 lanes, rows of 16 to 92 floats 4 lanes, the rest one.
-static int predict_group(int D) {
-  if (D % 4 != 0) return 1;
-  const int nv = D / 4;
-  return nv >= 24 ? 8 : (nv >= 4 ? 4 : 1);
-}
-
 int64_t pair_blocks(int64_t n, int D) {
   return (n * predict_group(D) + kPairBlock - 1) / kPairBlock;
 }
@@ -217,11 +226,9 @@ hipError_t launch_predict(const float *U, const float *V, int64_t M, int64_t N, 
                           float *pred, double *sse_blocks, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   if (pair_blocks(n, D) > 0x7fffffff || (sse_blocks && !r)) return hipErrorInvalidValue;
-  const int G = predict_group(D);
-  if (G == 8) return launch_predict_group<8>(U, V, M, N, D, n, users, items, r, pred, sse_blocks, s);
-  if (G == 4) return launch_predict_group<4>(U, V, M, N, D, n, users, items, r, pred, sse_blocks, s);
-  if (D % 4 == 0) return launch_predict_vw<4>(U, V, M, N, D, n, users, items, r, pred, sse_blocks, s);
-  if (D % 2 == 0) return launch_predict_vw<2>(U, V, M, N, D, n, users, items, r, pred, sse_blocks, s);
+  const int vw = predict_vec(D);
+  if (vw == 4) return launch_predict_vw<4>(U, V, M, N, D, n, users, items, r, pred, sse_blocks, s);
+  if (vw == 2) return launch_predict_vw<2>(U, V, M, N, D, n, users, items, r, pred, sse_blocks, s);
   return launch_predict_vw<1>(U, V, M, N, D, n, users, items, r, pred, sse_blocks, s);
 }
 
