@@ -795,7 +795,7 @@ als_status als_create(als_ctx **out, int64_t n_users, int64_t n_items, int64_t n
     CK(dalloc(&c->d_ne, max_rows * (int64_t)als::ne_floats(als::lane_width(D))));
   CK(dalloc(&c->d_fpad, (std::max(n_users, n_items) + 1) * (int64_t)c->DP));
   CK(dalloc(&c->d_sse_items, max_sse));
-  CK(dalloc(&c->d_partials, als::reduce_partials(max_tasks)));
+  CK(dalloc(&c->d_partials, std::max(als::reduce_partials(max_tasks), als::kSolveReduceBlocks)));
   CK(dalloc(&c->d_flag, 1));
   CK(dalloc(&c->d_ticket, 1));
   // written by the reduction kernels, so coherent and mapped
@@ -884,6 +884,19 @@ als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out
   const int64_t n_fixed = sp.n_fixed;
   const als::Hadamard &hd = sp.hd;
   const int side = sp.plan;
+  // a small one-lane solve also reduces the squared residuals, unless more rows are drawn
+  // after it, or the phases are timed one by one
+  als::SolveReduce red;
+  if (ctx->lane_solve && P.batches.size() == 1 &&
+      als::solve_blocks(P.batches[0].n_rows) <= als::kSolveReduceBlocks &&
+      !(pr.init && !P.zero_rows.empty()) && !(ctx->profiling && ctx->prof_mode == 1)) {
+    red.sse = ctx->d_sse_items;
+    red.n = (int64_t)P.gitems.size();
+    red.partial = ctx->d_partials;
+    red.ticket = ctx->d_ticket;
+    red.out = ctx->hd_sse_in + sp.sse_in_part;
+    red.host_flag = ctx->hd_flag;
+  }
   for (const Batch &b : P.batches) {
     double *sse = ctx->d_sse_items + b.gitem_off;
     if (ctx->lane_solve) {
@@ -898,7 +911,7 @@ als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out
         PhaseTimer t(ctx, 2);
         HIP_OR_FAIL(ctx, als::launch_solve_lane(ctx->D, P.d_rows + b.row_off, b.n_rows, b.n_split,
                                                 b.row_off, ctx->d_ws, ctx->d_ne, lambda,
-                                                out_factors, ctx->d_flag, pr, ctx->stream));
+                                                out_factors, ctx->d_flag, pr, red, ctx->stream));
       }
     } else {
       const bool clocks = ctx->phase_timing && side < 2;  // the clocks cover users and items
@@ -933,7 +946,7 @@ als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out
                                             ctx->d_prior_K, ctx->d_prior_mu32, ctx->d_prior_ok,
                                             pr.z, out_factors, ctx->d_flag, ctx->stream));
   }
-  {
+  if (!red.sse) {
     PhaseTimer t(ctx, 4);
     HIP_OR_FAIL(ctx, als::launch_reduce(ctx->d_sse_items, (int64_t)P.gitems.size(),
                                         ctx->d_partials, ctx->d_ticket,
@@ -1406,7 +1419,8 @@ als_status als_set_time_bins(als_ctx *ctx, int32_t n_bins, const int32_t *bins) 
     dfree(ctx->d_sse_items);
     dfree(ctx->d_partials);
     HIP_OR_FAIL(ctx, dalloc(&ctx->d_sse_items, max_sse));
-    HIP_OR_FAIL(ctx, dalloc(&ctx->d_partials, als::reduce_partials(max_tasks)));
+    HIP_OR_FAIL(ctx, dalloc(&ctx->d_partials,
+                            std::max(als::reduce_partials(max_tasks), als::kSolveReduceBlocks)));
   }
   ctx->n_bins = n_bins;
   return ALS_OK;

@@ -140,12 +140,30 @@ hipError_t launch_gram_ne(int D, const WorkItem *items, int64_t n_items, int64_t
                           const float *Fp, int64_t n_fixed, const float *Xold, float *ws,
                           float *ne, double *sse, const Hadamard &hd, hipStream_t s);
 
+// The reduction of n squared residuals inside the one-lane solve: partial sums (one per block,
+// at most kSolveReduceBlocks), ticket as for launch_reduce, and the mapped host addresses that
+// receive the total and the flag count. sse == nullptr: none.
+struct SolveReduce {
+  const double *sse = nullptr;
+  int64_t n = 0;
+  double *partial = nullptr;
+  int32_t *ticket = nullptr;
+  double *out = nullptr;
+  int32_t *host_flag = nullptr;
+};
+// With more blocks (64 rows each) their device-wide releases cost more than the reduction launch
+// that they save: 47 and 79 blocks (5000 x 3000) 133 us without and 128 with, 16 and 32 blocks
+// 53 and 46, but 782 and 1563 blocks 346 and 380, 157 and 313 blocks 127 and 142.
+constexpr int64_t kSolveReduceBlocks = 64;
+inline int64_t solve_blocks(int64_t n_rows) { return (n_rows + 63) / 64; }
+
 // One row per lane: regularise, Cholesky, solve, write (lanesolve.hip). Row i of
 // the launch uses record base + i; its first n_split rows are split rows whose
 // chunk records (in ws) are summed into their records first.
 hipError_t launch_solve_lane(int D, const RowTask *rows, int64_t n_rows, int64_t n_split,
                              int64_t base, const float *ws, float *ne, float lam, float *X,
-                             int32_t *flag, const RowPrior &pr, hipStream_t s);
+                             int32_t *flag, const RowPrior &pr, const SolveReduce &red,
+                             hipStream_t s);
 
 // Fixed-order sum of n doubles into *out (0 for n = 0); partials: double[reduce_partials(n)];
 // ticket: a device int32 that is zero before the first launch and that launches on one

@@ -18,7 +18,8 @@
 //                (Lambda / alpha and Lambda mu / alpha), and y gets z / sqrt(alpha)
 //                before the back substitution, which turns the solve into the
 //                conditional draw mu* + L*^{-T} z. The time chain of BPTF scales the
-//                image per row and adds a per-row right-hand side (RowPrior).
+//                image per row and adds a per-row right-hand side (RowPrior). With few
+//                rows it also reduces the squared residuals.
 // Records hold LD(LD+1)/2 + LD floats (LD = 16 or 20, the width the solve is
 // compiled for; padded features solve to zero), rounded up to a multiple of 4.
 #include "gram.h"
@@ -228,12 +229,16 @@ __global__ __launch_bounds__(256) void k_sum_records(const RowTask *__restrict__
         (v + s_part[0][q]) + (s_part[1][q] + s_part[2][q]);
 }
 
+// With red.sse the blocks also add up the entering-state squared residuals: each takes a run
+// of them while its records load, and the block that finishes last adds the runs' sums in
+// order (whichever block it is) and hands total and flag count to the host, in place of a
+// reduction launch of about 5 us.
 template <int LD, bool BAYES>
-__global__ __launch_bounds__(64) void k_solve_lane(const RowTask *__restrict__ rows, int64_t n_rows,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_solve_lane(const RowTask *__restrict__ rows, int64_t n_rows,
                                                    int64_t base, const float *__restrict__ ne,
                                                    int D, float lam, float *__restrict__ X,
-                                                   int32_t *__restrict__ flag_count,
-                                                   RowPrior pr) {
+                                                   int32_t *flag_count, RowPrior pr,
+                                                   SolveReduce red) {
   constexpr int NTRI = LD * (LD + 1) / 2;
   constexpr int NES = ne_floats(LD);
   constexpr int NQ = NES / 4;               // float4 of a record
@@ -245,6 +250,21 @@ __global__ __launch_bounds__(64) void k_solve_lane(const RowTask *__restrict__ r
   const int64_t first = (int64_t)blockIdx.x * 64;
   const int64_t i = first + lane;
   const int64_t nrec = n_rows - first < 64 ? n_rows - first : 64;  // >= 1
+  const RowTask rt = rows[i < n_rows ? i : n_rows - 1];
+  if (red.sse != nullptr) {
+    const int64_t per = (red.n + gridDim.x - 1) / gridDim.x;
+    const int64_t end = min((blockIdx.x + 1) * per, red.n);
+    double t = 0.0;
+    for (int64_t k = blockIdx.x * per + lane; k < end; k += 64) t += red.sse[k];
+    t = sum_wave_f64(t);
+    if (lane == 0)
+      __hip_atomic_store(&red.partial[blockIdx.x], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // the prior image is added on the way into LDS, four entries per lane: added to the system
+  // in registers, its 230 uniform values took 176 registers more and a wave of the two
+  __shared__ float s_scale[BAYES ? 64 : 1];
+  if constexpr (BAYES) s_scale[lane] = pr.scale_of(rt.row);
+  if constexpr (BAYES) wave_sync();
   const float4 *__restrict__ recs = reinterpret_cast<const float4 *>(ne) + (base + first) * NQ;
   float A[NTRI], b[LD];
   // The block's 64 records are contiguous: each slice is read with consecutive lanes on
@@ -260,7 +280,14 @@ __global__ __launch_bounds__(64) void k_solve_lane(const RowTask *__restrict__ r
         const int f = k * 64 + lane;
         const int rr = f / nq, pc = f - rr * nq;
         const int64_t rec = rr < nrec ? rr : nrec - 1;
-        s_rec[rr * STRIDE + pc] = recs[rec * NQ + q0 + pc];
+        float4 v = recs[rec * NQ + q0 + pc];
+        if constexpr (BAYES) {
+          const float4 im = reinterpret_cast<const float4 *>(pr.init)[q0 + pc];
+          const float cs = s_scale[rr < nrec ? rr : nrec - 1];
+          v = make_float4(fmaf(cs, im.x, v.x), fmaf(cs, im.y, v.y), fmaf(cs, im.z, v.z),
+                          fmaf(cs, im.w, v.w));
+        }
+        s_rec[rr * STRIDE + pc] = v;
       }
     }
     wave_sync();
@@ -279,16 +306,18 @@ __global__ __launch_bounds__(64) void k_solve_lane(const RowTask *__restrict__ r
     }
     wave_sync();  // the stage is refilled by the next slice
   }
-  if (i >= n_rows) return;
-  const RowTask rt = rows[i];
+  // the variates wait in the records' LDS: read between the substitutions, where the features
+  // past D end a basic block each, they spilled 97 registers
+  [[maybe_unused]] float *const zs = reinterpret_cast<float *>(s_rec) + lane;
+  static_assert(sizeof(float4) * STRIDE >= sizeof(float) * LD, "the variates fit");
   if constexpr (BAYES) {
-    // the prior image carries the identity on the padding; the time chain scales it per
-    // row and adds the row's own right-hand side
-    const float cs = pr.scale_of(rt.row);
+    const float *__restrict__ zr = pr.z + (int64_t)rt.row * D;
 #pragma unroll
-    for (int e = 0; e < NTRI; ++e) A[e] = fmaf(cs, pr.init[e], A[e]);
-#pragma unroll
-    for (int d = 0; d < LD; ++d) b[d] = fmaf(cs, pr.init[NTRI + d], b[d]);
+    for (int d = 0; d < LD; ++d) zs[d * 64] = d < D ? zr[d] : 0.f;
+  }
+  if constexpr (BAYES) {
+    // the prior image (already added) carries the identity on the padding; the time chain
+    // scales it per row and adds the row's own right-hand side
     if (pr.h0 != nullptr) {
       const float *__restrict__ hr = pr.h0 + (int64_t)rt.row * D;
 #pragma unroll
@@ -326,10 +355,9 @@ __global__ __launch_bounds__(64) void k_solve_lane(const RowTask *__restrict__ r
     for (int j = k + 1; j < LD; ++j) b[j] = fmaf(-A[tri<LD>(k, j)], b[k], b[j]);
   }
   if constexpr (BAYES) {
-    const float *__restrict__ zr = pr.z + (int64_t)rt.row * D;
 #pragma unroll
     for (int d = 0; d < LD; ++d)
-      if (d < D) b[d] = fmaf(pr.zscale, zr[d], b[d]);
+      b[d] = fmaf(pr.zscale, zs[d * 64], b[d]);
   }
   // U x = y (x overwrites b)
 #pragma unroll
@@ -341,14 +369,31 @@ __global__ __launch_bounds__(64) void k_solve_lane(const RowTask *__restrict__ r
   }
 #pragma unroll
   for (int d = 0; d < LD; ++d) bad |= !(fabsf(b[d]) < INFINITY);
-  if (bad) {
-    atomicAdd(flag_count, 1);
-    return;
-  }
-  float *__restrict__ xr = X + (int64_t)rt.row * D;
+  if (i < n_rows) {
+    if (bad) {
+      atomicAdd(flag_count, 1);
+    } else {
+      float *__restrict__ xr = X + (int64_t)rt.row * D;
 #pragma unroll
-  for (int d = 0; d < LD; ++d)
-    if (d < D) xr[d] = b[d];
+      for (int d = 0; d < LD; ++d)
+        if (d < D) xr[d] = b[d];
+    }
+  }
+  if (red.sse != nullptr) {
+    int done = 0;
+    if (lane == 0)
+      done = __hip_atomic_fetch_add(red.ticket, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    if (__shfl(done, 0) != (int)gridDim.x - 1) return;
+    double t = 0.0;
+    for (unsigned k = lane; k < gridDim.x; k += 64)
+      t += __hip_atomic_load(&red.partial[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    t = sum_wave_f64(t);
+    if (lane == 0) {
+      *red.out = t;
+      *red.host_flag = __hip_atomic_load(flag_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(red.ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
 }
 
 template <int DP, int LD, bool AUG>
@@ -396,19 +441,21 @@ hipError_t launch_gram_ne(int D, const WorkItem *items, int64_t n_items, int64_t
 template <int LD>
 static void launch_solve_lane_t(unsigned blocks, const RowTask *rows, int64_t n_rows, int64_t base,
                                 const float *ne, int D, float lam, float *X, int32_t *flag,
-                                const RowPrior &pr, hipStream_t s) {
+                                const RowPrior &pr, const SolveReduce &red, hipStream_t s) {
   if (pr.init)
     hipLaunchKernelGGL((k_solve_lane<LD, true>), dim3(blocks), dim3(64), 0, s, rows, n_rows, base,
-                       ne, D, lam, X, flag, pr);
+                       ne, D, lam, X, flag, pr, red);
   else
     hipLaunchKernelGGL((k_solve_lane<LD, false>), dim3(blocks), dim3(64), 0, s, rows, n_rows,
-                       base, ne, D, lam, X, flag, pr);
+                       base, ne, D, lam, X, flag, pr, red);
 }
 
 hipError_t launch_solve_lane(int D, const RowTask *rows, int64_t n_rows, int64_t n_split,
                              int64_t base, const float *ws, float *ne, float lam, float *X,
-                             int32_t *flag, const RowPrior &pr, hipStream_t s) {
+                             int32_t *flag, const RowPrior &pr, const SolveReduce &red,
+                             hipStream_t s) {
   if (n_rows <= 0) return hipSuccess;
+  if (red.sse && solve_blocks(n_rows) > kSolveReduceBlocks) return hipErrorInvalidValue;
   const int ld = lane_width(D);
   if (ld != 16 && ld != 20) return hipErrorInvalidValue;
   if (n_split > 0) {
@@ -421,11 +468,11 @@ hipError_t launch_solve_lane(int D, const RowTask *rows, int64_t n_rows, int64_t
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  const unsigned blocks = (unsigned)((n_rows + 63) / 64);
+  const unsigned blocks = (unsigned)solve_blocks(n_rows);
   if (ld == 16)
-    launch_solve_lane_t<16>(blocks, rows, n_rows, base, ne, D, lam, X, flag, pr, s);
+    launch_solve_lane_t<16>(blocks, rows, n_rows, base, ne, D, lam, X, flag, pr, red, s);
   else
-    launch_solve_lane_t<20>(blocks, rows, n_rows, base, ne, D, lam, X, flag, pr, s);
+    launch_solve_lane_t<20>(blocks, rows, n_rows, base, ne, D, lam, X, flag, pr, red, s);
   return hipGetLastError();
 }
 
