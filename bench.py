@@ -539,7 +539,8 @@ def run_workload(args, k):
                     frac=achieved / HBM_PEAK_GBS, kernel="k_gram_ne",
                     whole_step_frac=alg / elapsed / 1e9 / HBM_PEAK_GBS)
     else:
-        # fused row kernel + chunk kernel of split rows, priced on the Gram build alone: the
+        # fused row kernel (rows, chunks and split rows) + the sum of the split rows' chunks,
+        # priced on the Gram build alone: the
         # SYRK-convention Gram flops D (D + 1) and the right-hand side 2 D per rating (plus
         # the weight or the second factor's product). The residual dot and the Cholesky
         # with its two solves run in the same kernels but are not counted here; the
@@ -549,7 +550,7 @@ def run_workload(args, k):
         alg = halves * r.nnz * (D * (D + 1) + 2 * D + wflops)
         achieved = alg / (k_ms * 1e-3) / 1e12
         roof = dict(bound="mfma", achieved=achieved, peak=MFMA_F32_PEAK_TFS, unit="TFLOP/s",
-                    frac=achieved / MFMA_F32_PEAK_TFS, kernel="k_rows+k_gram_chunks",
+                    frac=achieved / MFMA_F32_PEAK_TFS, kernel="k_rows+k_sum_slots",
                     flops="SYRK Gram + right-hand side per rating",
                     whole_step_frac=alg / elapsed / 1e12 / MFMA_F32_PEAK_TFS,
                     chol_flops_per_step=rows_with * (D ** 3 / 3.0 + 2.0 * D * D))
@@ -557,7 +558,7 @@ def run_workload(args, k):
                 traffic=measured_traffic(workload_name, roof["kernel"]), dominant_phase=dominant)
     gram_phase = None
     if gram_share is not None:
-        # Gram phase: the chunk kernel plus the share of the fused row kernel's wavefront
+        # Gram phase: the sum of the chunks plus the share of the fused row kernel's wavefront
         # time spent before the factorisation (gather, Gram, RHS, residuals); flops in
         # the SYRK convention plus the right-hand side
         g_ms = (prof["gather"][0] + gram_share * prof["solve"][0]) / args.steps
@@ -567,7 +568,7 @@ def run_workload(args, k):
                           peak=MFMA_F32_PEAK_TFS, unit="TFLOP/s", frac=g_tf / MFMA_F32_PEAK_TFS,
                           row_kernel_gram_share=gram_share,
                           cycles_per_row=phase_cycles,
-                          method="chunk-kernel time plus the row kernel's time scaled by the "
+                          method="chunk-sum time plus the row kernel's time scaled by the "
                                  "share of wavefront clock cycles before the factorisation")
 
     # (the held-out leg scores u . v pairs: the matrix model's prediction, so not for the

@@ -135,11 +135,13 @@ template <int DP>
 struct RowCfg {
   static constexpr int T = DP / 16;
   static constexpr int NT = T * (T + 1) / 2;
-  // steps per gathered block. Wide rows keep two blocks of one step (four ratings) in flight:
+  // Steps per gathered block. Narrow rows gather a group at once. Wide rows keep two blocks of one step (four ratings) in flight:
   // blocks of eight to two steps hid no more latency beside the other waves and took the
   // registers of one of them (at eight tiles they spilled: tensor ALS, D = 128, 10.7 against
   // 8.3 ms)
   static constexpr int STEPS = T <= 2 ? 16 : 1;
+  // group buffers in LDS
+  static constexpr int BUFS = T <= 2 ? 1 : 2;
 };
 
 template <int V>
@@ -157,13 +159,16 @@ __device__ __forceinline__ void unroll_blocks(F &f) {
 
 // Per-wave LDS staging of a 64-rating group's column indices and ratings, transposed
 // so that lane (kq, c) finds the values of its steps s (ratings 4 s + kq) contiguously
-// at [kq * 16 + s]; two buffers let the next group be staged while the current one is
-// still read.
-struct GroupStage {
-  int32_t j[2][64];
-  float r[2][64];
-  float w[2][64];   // per-rating weights (weighted ALS only)
-  int32_t t[2][64]; // second index of each rating (tensor ALS only)
+// at [kq * 16 + s]; with two buffers the next group is staged while the current one is
+// still read. Only what the kernel's method needs: 4.9 KB with one buffer lets eight waves of
+// the one-tile Gram kernel share a SIMD, where 6.4 KB let six (10M ratings, D = 8 240 and 225 us
+// a sweep, D = 16 249 and 237).
+template <int NBUF, bool WT, bool TS>
+struct GroupStageT {
+  int32_t j[NBUF][64];
+  float r[NBUF][64];
+  float w[WT ? NBUF : 1][WT ? 64 : 1];    // per-rating weights (weighted ALS only)
+  int32_t t[TS ? NBUF : 1][TS ? 64 : 1];  // second index of each rating (tensor ALS only)
   // the 16 step partials of every lane, transposed for the end-of-group sums: row group kq,
   // feature lane c, step s at [kq * kRedGroup + c * kRedRow + s]; the odd row stride keeps
   // both the row-wise stores and the column-wise loads free of bank conflicts
@@ -181,8 +186,8 @@ struct GroupLanes {
 };
 
 // Stage the group held one rating per lane (lane L holds rating L of the group).
-template <bool WT, bool TS = false>
-__device__ __forceinline__ void stage_group(GroupStage &st, int buf, const GroupLanes &g) {
+template <bool WT, bool TS, class Stage>
+__device__ __forceinline__ void stage_group(Stage &st, int buf, const GroupLanes &g) {
   const int lane = threadIdx.x & 63;
   const int at = (lane & 3) * 16 + (lane >> 2);
   st.j[buf][at] = g.j;
@@ -249,10 +254,10 @@ __device__ __forceinline__ GroupLanes first_group(const int32_t *__restrict__ ip
 // the product's padding zero.
 // With STRIP, sb[u] receives feature 16 (T - 1) + (c & 3) of the lane's rating: the
 // operand that every 4x4 block of the strip products in mma_block multiplies by.
-template <int DP, int STEPS, bool AUG, bool WT, bool TS = false, bool STRIP = false>
+template <int DP, int STEPS, bool AUG, bool WT, bool TS = false, bool STRIP = false, class Stage>
 __device__ __forceinline__ void gather_block(float (&a)[STEPS][DP / 16], float (&sb)[STEPS],
                                              float (&r)[STEPS], float (&wt)[STEPS],
-                                             const GroupStage &st, int buf, int s0,
+                                             const Stage &st, int buf, int s0,
                                              const float *__restrict__ Fp,
                                              const float *__restrict__ Tp, bool aug_lane) {
   constexpr int T = DP / 16;
@@ -260,8 +265,8 @@ __device__ __forceinline__ void gather_block(float (&a)[STEPS][DP / 16], float (
   const int kq = lane >> 4, c = lane & 15;
   const int32_t *__restrict__ sj = &st.j[buf][kq * 16 + s0];
   const float *__restrict__ sr = &st.r[buf][kq * 16 + s0];
-  const float *__restrict__ sw = &st.w[buf][kq * 16 + s0];
-  const int32_t *__restrict__ stt = &st.t[buf][kq * 16 + s0];
+  const float *__restrict__ sw = WT ? &st.w[buf][kq * 16 + s0] : nullptr;
+  const int32_t *__restrict__ stt = TS ? &st.t[buf][kq * 16 + s0] : nullptr;
 #pragma unroll
   for (int u = 0; u < STEPS; ++u) {
     const int j = sj[u];
@@ -372,7 +377,8 @@ __device__ __forceinline__ void mma_block(floatx4 (&acc)[RowCfg<DP>::NT],
 }
 
 // Where a lane's share of step s's predictions goes in the group's LDS area.
-__device__ __forceinline__ float *step_partials(GroupStage &st) {
+template <class Stage>
+__device__ __forceinline__ float *step_partials(Stage &st) {
   const int lane = threadIdx.x & 63;
   return &st.red[(lane >> 4) * kRedGroup + (lane & 15) * kRedRow];
 }
@@ -382,8 +388,8 @@ __device__ __forceinline__ float *step_partials(GroupStage &st) {
 // feature lanes' shares of step c in lane order, which gives the full prediction of rating
 // g + 4 c + kq; its squared residual is added to sse. Shares of steps past the item's end may
 // be stale; their sums are dropped.
-__device__ __forceinline__ void group_residuals(GroupStage &st, int buf, int g, int n,
-                                                double &sse) {
+template <class Stage>
+__device__ __forceinline__ void group_residuals(Stage &st, int buf, int g, int n, double &sse) {
   const int lane = threadIdx.x & 63;
   const int kq = lane >> 4, c = lane & 15;
   wave_sync();
@@ -408,7 +414,8 @@ __device__ __forceinline__ void group_residuals(GroupStage &st, int buf, int g, 
 // gv: the first group's lanes (group_lanes(.., 0, ..)), loaded by the caller.
 // Ratings are taken in groups of 64, each gathered in blocks of STEPS steps (four
 // ratings per step).
-//  - Narrow rows (T <= 2): one block per group, gathered and then multiplied.
+//  - Narrow rows (T <= 2): one block per group, gathered and then multiplied. (Blocks of eight
+//    and four steps for shorter groups were slower at two tiles, by 2 to 20 %.)
 //  - Wider rows: two block buffers; the gather of the next block (of this group, or
 //    the first block of the next group) is issued before the MFMAs of the current
 //    one, so that its latency hides behind them. The blocks of the last group that
@@ -418,7 +425,8 @@ __device__ __forceinline__ void group_residuals(GroupStage &st, int buf, int g, 
 // only the right-hand side of features 16..19), else unused.
 // STRIP: the last tile column in strip form (mma_block); the caller finishes it with
 // strip_finish.
-template <int DP, bool AUG, bool WT, bool TS = false, bool CORNER = false, bool STRIP = false>
+template <int DP, bool AUG, bool WT, bool TS = false, bool CORNER = false, bool STRIP = false,
+          class Stage>
 __device__ __forceinline__ void gram_accumulate(floatx4 (&acc)[RowCfg<DP>::NT],
                                                 float (&rhs)[RowCfg<DP>::T],
                                                 const float (&xo)[RowCfg<DP>::T], double &sse,
@@ -428,7 +436,7 @@ __device__ __forceinline__ void gram_accumulate(floatx4 (&acc)[RowCfg<DP>::NT],
                                                 const int32_t *__restrict__ tp, int n,
                                                 const float *__restrict__ Fp,
                                                 const float *__restrict__ Tp, int zrow,
-                                                int aug_c, GroupStage &st, GroupLanes gv,
+                                                int aug_c, Stage &st, GroupLanes gv,
                                                 float &corner, int cx, int cy) {
   using C = RowCfg<DP>;
   constexpr int T = C::T, STEPS = C::STEPS, NB = 16 / STEPS;
@@ -444,17 +452,15 @@ __device__ __forceinline__ void gram_accumulate(floatx4 (&acc)[RowCfg<DP>::NT],
       float pi[16];
 #pragma unroll
       for (int u = 0; u < 16; ++u) pi[u] = 0.f;
-#pragma unroll
-      for (int s0 = 0; s0 < 16; s0 += STEPS) {
-        if (s0 < steps) {
-          float a[STEPS][T];
-          float sb[STEPS], r[STEPS], w[STEPS];
-          gather_block<DP, STEPS, AUG, WT, TS>(a, sb, r, w, st, 0, s0, Fp, Tp, aug_lane);
-          auto put = [&](int step, float p) { pi[step] = p; };
-          mma_block<DP, STEPS, AUG, WT, CORNER, STRIP, CORNER && !TS>(acc, rhs, xo, put, a, sb, r, w, s0, steps,
-                                                       corner, cx, cy);
-        }
-      }
+      auto put = [&](int step, float p) { pi[step] = p; };
+      auto block = [&](auto nc) {
+        constexpr int N = decltype(nc)::value;
+        float a[N][T], sb[N], r[N], w[N];
+        gather_block<DP, N, AUG, WT, TS>(a, sb, r, w, st, 0, 0, Fp, Tp, aug_lane);
+        mma_block<DP, N, AUG, WT, CORNER, STRIP, CORNER && !TS>(acc, rhs, xo, put, a, sb, r, w, 0,
+                                                                steps, corner, cx, cy);
+      };
+      block(IntC<STEPS>{});
       float *const red = step_partials(st);
 #pragma unroll
       for (int u = 0; u < 16; ++u) red[u] = pi[u];

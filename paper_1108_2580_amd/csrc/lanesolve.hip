@@ -40,7 +40,6 @@ namespace als {
 constexpr int kImgTile = 0, kImgStrip = 256, kImgCorner = 320, kImgRhs = 336, kImgZero = 356,
               kImgSink = 360, kImgFloats = 364;
 constexpr int kRecordEntries20 = ne_floats(20);
-static_assert(sizeof(GroupStage) >= sizeof(float) * kImgFloats, "the record image fits");
 // Source in the image of every record entry (packed upper triangle of G, then b).
 struct __attribute__((aligned(8))) RecordMap20 {
   uint16_t src[kRecordEntries20];
@@ -79,7 +78,9 @@ void k_gram_ne(const WorkItem *__restrict__ items, int64_t n_chunk_items,
   // the tile above it, which holds four used features, goes to 4 x 4 strips (STRIP)
   constexpr bool CORNER = AUG && T == 2 && LD == 20;
   constexpr bool STRIP = CORNER;
-  __shared__ __attribute__((aligned(16))) GroupStage s_stage;
+  using Stage = GroupStageT<C::BUFS, WT, TS>;
+  static_assert(sizeof(Stage) >= sizeof(float) * kImgFloats, "the record image fits");
+  __shared__ __attribute__((aligned(16))) Stage s_stage;
   const WorkItem it = items[blockIdx.x];
   const int lane = threadIdx.x, kq = lane >> 4, c = lane & 15;
   floatx4 acc[NT];

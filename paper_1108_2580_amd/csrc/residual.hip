@@ -25,7 +25,7 @@ __global__ __launch_bounds__(64) void k_resid(const WorkItem *__restrict__ items
                                               const float *__restrict__ X, int D,
                                               double *__restrict__ sse_items, Hadamard hd) {
   constexpr int T = DP / 16;
-  __shared__ GroupStage st;
+  __shared__ GroupStageT<1, false, TS> st;
   const WorkItem it = items[blockIdx.x];
   const int lane = threadIdx.x, c = lane & 15;
   float xo[T];

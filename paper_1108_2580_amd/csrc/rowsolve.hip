@@ -184,14 +184,15 @@ __global__ __launch_bounds__(64, (kRowWaves<DP, AUG, BAYES>)) void k_rows(
   constexpr bool kTurns = T <= 7;
   constexpr int kPanelBytes = 4 * T * 16 * 16, kUdBytes = NPAN * 80;
   constexpr int kTurnBytes = kPanelBytes + kUdBytes + 256;
-  constexpr int kStageBytes = sizeof(GroupStage);
+  using Stage = GroupStageT<C::BUFS, WT, TS>;
+  constexpr int kStageBytes = sizeof(Stage);
   __shared__ __attribute__((aligned(16))) char
       s_turns[!kTurns ? 16 : kTurnBytes > kStageBytes ? kTurnBytes : kStageBytes];
   __shared__ __attribute__((aligned(16))) char s_panel[kTurns ? 16 : kPanelBytes];
   __shared__ __attribute__((aligned(16))) char s_ud[kTurns ? 16 : kUdBytes];
   __shared__ __attribute__((aligned(16))) char s_dummy[kTurns ? 16 : 256];
   __shared__ __attribute__((aligned(16))) char s_own[kTurns ? 16 : kStageBytes];
-  GroupStage &s_stage = *reinterpret_cast<GroupStage *>(kTurns ? s_turns : s_own);
+  Stage &s_stage = *reinterpret_cast<Stage *>(kTurns ? s_turns : s_own);
   auto &panel = *reinterpret_cast<floatx4(*)[4][T][16]>(kTurns ? s_turns : s_panel);
   auto &ud = *reinterpret_cast<float(*)[NPAN][20]>(kTurns ? s_turns + kPanelBytes : s_ud);
   auto &dummy =
