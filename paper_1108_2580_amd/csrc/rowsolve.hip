@@ -161,46 +161,51 @@ constexpr int kRowWaves = BAYES && !AUG              ? 2
 // summed chunks are in its first slot. Chunks share the launch of the whole rows so that
 // neither leaves the chip idle at its end: as a launch of their own, few chunks kept most
 // SIMDs waiting (23 chunks of 4096 ratings at D = 50 took 182 us).
-template <int DP, bool AUG, bool WT, bool BAYES, bool TS, bool STRIP = false>
-__global__ __launch_bounds__(64, (kRowWaves<DP, AUG, BAYES>)) void k_rows(
-    const WorkItem *__restrict__ items, int64_t n_chunks, const RowTask *__restrict__ rows,
-    const int32_t *__restrict__ idx,
-    const uint8_t *__restrict__ val, const float *__restrict__ wts,
-    const float *__restrict__ Fp, int zrow,
-    float *__restrict__ ws, int D, float lam, float *__restrict__ X_io,
-    double *__restrict__ sse_out,
-    int32_t *__restrict__ flag_count, double *__restrict__ cyc_gram,
-    double *__restrict__ cyc_solve, RowPrior pr, Hadamard hd) {
+enum TaskRole { kAnyTask, kChunkTask, kRowTask, kSplitRowTask };
+
+// LDS of a wave: the gather's staging, and the factorisation's area: tile row I0 of the panel
+// step, as published by each row group [row group][tile column][lane column]; per panel, M as a
+// full 4 x 4 row-major block (zeros above the diagonal), then y_p; a sink for the stores of
+// lanes without an entry. Up to seven tiles the two take turns in one piece (6.4 to 9.6 KB a
+// wave), so that LDS does not limit the waves per SIMD; eight tiles run two waves, and there
+// the wait between the turns only costs (0.5 %).
+template <int DP, bool WT, bool TS>
+struct RowLds {
+  using Stage = GroupStageT<RowCfg<DP>::BUFS, WT, TS>;
+  static constexpr bool kTurns = RowCfg<DP>::T <= 7;
+  static constexpr int kStage = (sizeof(Stage) + 15) / 16 * 16;
+  static constexpr int kPanel = 4 * RowCfg<DP>::T * 16 * 16, kUd = DP / 4 * 80;
+  static constexpr int kFactor = kPanel + kUd + 256;
+  static constexpr int kPanelAt = kTurns ? 0 : kStage;
+  static constexpr int kBytes = !kTurns ? kStage + kFactor : kFactor > kStage ? kFactor : kStage;
+};
+
+// One task of k_rows. ROLE: its kind, where the code is for one kind alone (kRolesApart).
+template <int DP, bool AUG, bool WT, bool BAYES, bool TS, bool STRIP, int ROLE>
+__device__ __forceinline__ void rows_task(
+    char *lds,
+    const WorkItem *items, int64_t n_chunks, const RowTask *rows,
+    const int32_t *idx,
+    const uint8_t *val, const float *wts,
+    const float *Fp, int zrow,
+    float *ws, int D, float lam, float *X_io,
+    double *sse_out,
+    int32_t *flag_count, double *cyc_gram,
+    double *cyc_solve, RowPrior pr, Hadamard hd) {
   const uint64_t t_start = __builtin_readcyclecounter();
   using C = RowCfg<DP>;
+  using L = RowLds<DP, WT, TS>;
   constexpr int T = C::T, NT = C::NT;
   constexpr int NPAN = DP / 4;
-  // LDS of the factorisation: tile row I0 of the panel step, as published by each row group
-  // [row group][tile column][lane column]; per panel, M as a full 4 x 4 row-major block (zeros
-  // above the diagonal), then y_p; a sink for the stores of lanes without an entry. Up to
-  // seven tiles it takes turns with the gather's staging in one piece (6.4 to 9.6 KB a wave),
-  // so that LDS does not limit the waves per SIMD; eight tiles run two waves, and there the
-  // wait between the turns only costs (0.5 %).
-  constexpr bool kTurns = T <= 7;
-  constexpr int kPanelBytes = 4 * T * 16 * 16, kUdBytes = NPAN * 80;
-  constexpr int kTurnBytes = kPanelBytes + kUdBytes + 256;
-  using Stage = GroupStageT<C::BUFS, WT, TS>;
-  constexpr int kStageBytes = sizeof(Stage);
-  __shared__ __attribute__((aligned(16))) char
-      s_turns[!kTurns ? 16 : kTurnBytes > kStageBytes ? kTurnBytes : kStageBytes];
-  __shared__ __attribute__((aligned(16))) char s_panel[kTurns ? 16 : kPanelBytes];
-  __shared__ __attribute__((aligned(16))) char s_ud[kTurns ? 16 : kUdBytes];
-  __shared__ __attribute__((aligned(16))) char s_dummy[kTurns ? 16 : 256];
-  __shared__ __attribute__((aligned(16))) char s_own[kTurns ? 16 : kStageBytes];
-  Stage &s_stage = *reinterpret_cast<Stage *>(kTurns ? s_turns : s_own);
-  auto &panel = *reinterpret_cast<floatx4(*)[4][T][16]>(kTurns ? s_turns : s_panel);
-  auto &ud = *reinterpret_cast<float(*)[NPAN][20]>(kTurns ? s_turns + kPanelBytes : s_ud);
-  auto &dummy =
-      *reinterpret_cast<float(*)[64]>(kTurns ? s_turns + kPanelBytes + kUdBytes : s_dummy);
+  auto &s_stage = *reinterpret_cast<typename L::Stage *>(lds);
+  auto &panel = *reinterpret_cast<floatx4(*)[4][T][16]>(lds + L::kPanelAt);
+  auto &ud = *reinterpret_cast<float(*)[NPAN][20]>(lds + L::kPanelAt + L::kPanel);
+  auto &dummy = *reinterpret_cast<float(*)[64]>(lds + L::kPanelAt + L::kPanel + L::kUd);
 
   // one task per workgroup, whose record is then held in scalar registers
   const int64_t task = blockIdx.x;
-  const bool summed = items == nullptr, chunk = task < n_chunks;
+  const bool summed = ROLE == kAnyTask ? items == nullptr : ROLE == kSplitRowTask;
+  const bool chunk = ROLE == kAnyTask ? task < n_chunks : ROLE == kChunkTask;
   int64_t start = 0, slot;
   int32_t row, deg;
   if (summed) {
@@ -346,7 +351,7 @@ __global__ __launch_bounds__(64, (kRowWaves<DP, AUG, BAYES>)) void k_rows(
   }
 
   const uint64_t t_gram = __builtin_readcyclecounter();
-  if constexpr (kTurns) wave_sync();  // the panels overwrite the gather's staging
+  if constexpr (L::kTurns) wave_sync();  // the panels overwrite the gather's staging
 
   // ---- factorisation A = U^T U with forward substitution U^T y = b ------------------------
   // Panel step (I0, g) of rows p0 .. p0 + 3, p0 = 16 I0 + 4 g. Its update of the trailing
@@ -651,6 +656,46 @@ __global__ __launch_bounds__(64, (kRowWaves<DP, AUG, BAYES>)) void k_rows(
     const uint64_t t_end = __builtin_readcyclecounter();
     cyc_gram[task] = (double)(t_gram - t_start);
     cyc_solve[task] = (double)(t_end - t_gram);
+  }
+}
+
+// Whether the three kinds of task take code of their own rather than share it. Shared code keeps
+// what each of them needs alive across the Gram, and where the tiles and the explicit
+// right-hand side fill the registers already, the Gibbs draw's prior image on top spilled 45 to
+// 148 of them; apart, nothing spills. Us per pair of Gibbs half-sweeps, shared and apart:
+// 6M uniform ratings BPMF D = 112 2880 and 2815, D = 128 3710 and 3550, BPTF 4640 and 4085, 5690
+// and 5045; 5M Zipf ratings (mostly chunks) BPMF 2480 and 2430, 3185 and 3045. A launch of its
+// own for each kind, instead of a branch, took 2795 and 3850 on the latter. The other instances
+// share: up to six tiles nothing spills either way, and plain and weighted ALS at D = 112 gain
+// more from the third wave than its spills cost (2610 and 2670 us a sweep with up to 95 spilled,
+// 2745 and 2845 at two waves with none).
+template <int DP, bool AUG, bool BAYES>
+constexpr bool kRolesApart = BAYES && !AUG && DP >= 112;
+
+template <int DP, bool AUG, bool WT, bool BAYES, bool TS, bool STRIP = false>
+__global__ __launch_bounds__(64, (kRowWaves<DP, AUG, BAYES>)) void k_rows(
+    const WorkItem *__restrict__ items, int64_t n_chunks, const RowTask *__restrict__ rows,
+    const int32_t *__restrict__ idx,
+    const uint8_t *__restrict__ val, const float *__restrict__ wts,
+    const float *__restrict__ Fp, int zrow,
+    float *__restrict__ ws, int D, float lam, float *__restrict__ X_io,
+    double *__restrict__ sse_out,
+    int32_t *__restrict__ flag_count, double *__restrict__ cyc_gram,
+    double *__restrict__ cyc_solve, RowPrior pr, Hadamard hd) {
+  __shared__ __attribute__((aligned(16))) char lds[RowLds<DP, WT, TS>::kBytes];
+  auto task = [&](auto role) {
+    rows_task<DP, AUG, WT, BAYES, TS, STRIP, decltype(role)::value>(
+        lds, items, n_chunks, rows, idx, val, wts, Fp, zrow, ws, D, lam, X_io, sse_out,
+        flag_count, cyc_gram, cyc_solve, pr, hd);
+  };
+  if constexpr (!kRolesApart<DP, AUG, BAYES>) {
+    task(IntC<kAnyTask>{});
+  } else if (items == nullptr) {
+    task(IntC<kSplitRowTask>{});
+  } else if ((int64_t)blockIdx.x < n_chunks) {
+    task(IntC<kChunkTask>{});
+  } else {
+    task(IntC<kRowTask>{});
   }
 }
 
