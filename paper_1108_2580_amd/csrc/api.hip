@@ -25,6 +25,20 @@
 using als::RowTask;
 using als::WorkItem;
 
+namespace als {
+
+int64_t order_items(WorkItem *items, int64_t n_chunks, int64_t n) {
+  int32_t longest = 0;
+  for (int64_t i = 0; i < n_chunks; ++i) longest = std::max(longest, items[i].len);
+  int64_t lead = 0;
+  if (n_chunks > 0)
+    while (n_chunks + lead < n && items[n_chunks + lead].len > longest) ++lead;
+  std::rotate(items, items + n_chunks, items + n_chunks + lead);
+  return lead;
+}
+
+}  // namespace als
+
 namespace {
 
 // Ratings per chunk of a split row; rows of more than two chunks' ratings are split.
@@ -44,7 +58,8 @@ constexpr int64_t kCscTableEntries = 1LL << 29;
 
 struct Batch {
   int64_t gitem_off;  // first gather item of the batch
-  int64_t n_gchunks;  // its chunks of split rows (they come first)
+  int64_t chunk_off;  // first chunk of a split row among them
+  int64_t n_gchunks;  // its chunks of split rows
   int64_t n_gitems;   // chunks + unsplit rows
   int64_t row_off, n_rows;
   int64_t n_split;    // the batch's first n_split rows are split rows
@@ -60,7 +75,7 @@ struct SidePlan {
   int64_t max_deg = 0;
   int64_t max_slots = 0;    // largest batch, in slots
   std::vector<Batch> batches;
-  std::vector<WorkItem> gitems;  // per batch: chunks of split rows, then unsplit rows
+  std::vector<WorkItem> gitems;  // per batch, in order_items' order
   std::vector<RowTask> rows;     // every row with ratings, batch-major, descending degree
   WorkItem *d_gitems = nullptr;
   RowTask *d_rows = nullptr;
@@ -341,7 +356,7 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
     if (first < (int64_t)order.size()) spans.push_back({first, (int64_t)order.size()});
   }
   for (const auto &span : spans) {
-    Batch b{(int64_t)P.gitems.size(), 0, 0, (int64_t)P.rows.size(), 0, 0, P.split_rows, 0};
+    Batch b{(int64_t)P.gitems.size(), 0, 0, 0, (int64_t)P.rows.size(), 0, 0, P.split_rows, 0};
     // chunks of the batch's split rows
     for (int64_t k = span.first; k < span.second; ++k) {
       const int32_t s = order[k];
@@ -382,10 +397,12 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
       it.start = ptr[s];
       it.len = (int32_t)d;
       it.row = s;
-      it.slot = rt.slot0;
+      it.slot = ~rt.slot0;
       P.gitems.push_back(it);
     }
     b.n_gitems = (int64_t)P.gitems.size() - b.gitem_off;
+    b.chunk_off = b.gitem_off + als::order_items(P.gitems.data() + b.gitem_off, b.n_gchunks,
+                                                 b.n_gitems);
     b.n_rows = (int64_t)P.rows.size() - b.row_off;
     P.n_chunks += b.n_gchunks;
     P.batches.push_back(b);
@@ -426,8 +443,8 @@ als_status order_chunks(als_ctx *ctx, SidePlan &P, const int32_t *d_idx, int64_t
   for (const Batch &b : P.batches) {
     if (b.n_gchunks == 0) continue;
     // a stable counting sort over the table's buckets
-    const WorkItem *src = P.gitems.data() + b.gitem_off;
-    const int32_t *key = first.data() + b.gitem_off;
+    const WorkItem *src = P.gitems.data() + b.chunk_off;
+    const int32_t *key = first.data() + b.chunk_off;
     std::vector<int64_t> at(kBuckets + 1, 0);
     auto bucket = [&](int64_t q) { return (int64_t)key[q] * kBuckets / std::max<int64_t>(n_fixed, 1); };
     for (int64_t q = 0; q < b.n_gchunks; ++q) at[bucket(q) + 1] += 1;
@@ -441,8 +458,8 @@ als_status order_chunks(als_ctx *ctx, SidePlan &P, const int32_t *d_idx, int64_t
       const int64_t k = r < full * per ? r % per : (r - full * per) % std::max<int64_t>(per - 1, 1);
       out[k * kXcds + x] = src[q];
     }
-    std::copy(out.begin(), out.end(), P.gitems.begin() + b.gitem_off);
-    HIP_OR_FAIL(ctx, hipMemcpy(P.d_gitems + b.gitem_off, out.data(),
+    std::copy(out.begin(), out.end(), P.gitems.begin() + b.chunk_off);
+    HIP_OR_FAIL(ctx, hipMemcpy(P.d_gitems + b.chunk_off, out.data(),
                                sizeof(WorkItem) * b.n_gchunks, hipMemcpyHostToDevice));
   }
   return ALS_OK;
@@ -899,10 +916,9 @@ als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out
     if (ctx->lane_solve) {
       {
         PhaseTimer t(ctx, 1);
-        HIP_OR_FAIL(ctx, als::launch_gram_ne(ctx->D, P.d_gitems + b.gitem_off, b.n_gitems,
-                                             b.n_gchunks, idx, val, wts, ctx->d_fpad, n_fixed,
-                                             out_factors, ctx->d_ws, ctx->d_ne, sse, hd,
-                                             ctx->stream));
+        HIP_OR_FAIL(ctx, als::launch_gram_ne(ctx->D, P.d_gitems + b.gitem_off, b.n_gitems, idx,
+                                             val, wts, ctx->d_fpad, n_fixed, out_factors,
+                                             ctx->d_ws, ctx->d_ne, sse, hd, ctx->stream));
       }
       {
         PhaseTimer t(ctx, 2);
@@ -916,10 +932,10 @@ als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out
       double *cs = clocks ? cg + ctx->cyc_cap : nullptr;
       {
         PhaseTimer t(ctx, 2);
-        HIP_OR_FAIL(ctx, als::launch_rows(ctx->DP, P.d_gitems + b.gitem_off, b.n_gchunks, nullptr,
-                                          b.n_gitems, idx, val, wts, ctx->d_fpad, n_fixed,
-                                          ctx->d_ws, ctx->D, lambda, out_factors, sse,
-                                          ctx->d_flag, cg, cs, pr, hd, ctx->stream));
+        HIP_OR_FAIL(ctx, als::launch_rows(ctx->DP, P.d_gitems + b.gitem_off, nullptr, b.n_gitems,
+                                          idx, val, wts, ctx->d_fpad, n_fixed, ctx->d_ws, ctx->D,
+                                          lambda, out_factors, sse, ctx->d_flag, cg, cs, pr, hd,
+                                          ctx->stream));
       }
       if (b.n_split > 0) {
         {
@@ -930,7 +946,7 @@ als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out
         PhaseTimer t(ctx, 2);
         cg = clocks ? ctx->d_cyc + (int64_t)P.gitems.size() + b.split_off : nullptr;
         cs = clocks ? cg + ctx->cyc_cap : nullptr;
-        HIP_OR_FAIL(ctx, als::launch_rows(ctx->DP, nullptr, 0, P.d_rows + b.row_off, b.n_split,
+        HIP_OR_FAIL(ctx, als::launch_rows(ctx->DP, nullptr, P.d_rows + b.row_off, b.n_split,
                                           idx, val, wts, ctx->d_fpad, n_fixed, ctx->d_ws, ctx->D,
                                           lambda, out_factors, sse, ctx->d_flag, cg, cs, pr, hd,
                                           ctx->stream));

@@ -11,11 +11,20 @@ namespace als {
 // One unit of Gram work: a whole row, or one chunk of a split ("hub") row.
 struct WorkItem {
   int64_t start;  // first rating of the item, offset into the side's idx/val arrays
-  int64_t slot;   // workspace slot of the item's partial normal equations (batch local)
+  int64_t slot;   // chunk: workspace slot of its partial normal equations (batch local); whole
+                  // row: ~ the row's record, so below zero
   int32_t len;    // ratings in the item
   int32_t row;    // solved-side row the item belongs to
 };
 static_assert(sizeof(WorkItem) == 24, "WorkItem layout");
+
+// Order of a batch's items (api.hip): given its chunks and then its whole rows by descending
+// length, the rows longer than every chunk move ahead of the chunks, so that the largest work
+// starts first; returns their number. Behind the chunks, a few rows just under the splitting
+// threshold ran on alone at the end (2500 rows of about 4000 ratings, nine of them whole, D =
+// 33: 457 us a half-sweep behind, 412 ahead; of about 1200, 153 and 132; time bins of 3300
+// ratings, D = 10, 178 and 160; 1500 rows of 3300, D = 100, 856 and 774).
+int64_t order_items(WorkItem *items, int64_t n_chunks, int64_t n);
 
 // One row to solve, from its record (narrow widths) or its workspace slots (split rows).
 struct RowTask {
@@ -99,9 +108,8 @@ hipError_t launch_stage_fixed(const float *F, int64_t n, float *Fp, const float 
 
 // Fused per-row normal equations, regularisation, Cholesky and solves; X is read
 // (entering state) and overwritten in place (rowsolve.hip). Exactly one of items and rows:
-//  - items: n_tasks gather items. The first n_chunks are chunks of split rows, whose partial
-//    normal equations go to their workspace slots; the others are whole rows, solved at
-//    once. Item i writes its entering-state squared residuals to sse[i].
+//  - items: n_tasks gather items: chunks of split rows, whose partial normal equations go to
+//    their workspace slots, and whole rows, solved at once. Item i writes its entering-state squared residuals to sse[i].
 //  - rows: n_tasks split rows, whose first slots launch_sum_slots has filled.
 // wts (here and below): per-rating weights aligned with idx / val for weighted ALS,
 // or null for plain ALS.
@@ -110,8 +118,8 @@ hipError_t launch_stage_fixed(const float *F, int64_t n, float *Fp, const float 
 // residuals, or the read of the summed chunks) and from there on (factorisation, solves,
 // write); a measurement aid that leaves the results unchanged.
 // pr: the Bayesian prior (Gibbs half-sweep) or a default RowPrior (ALS; lam is used).
-hipError_t launch_rows(int dp, const WorkItem *items, int64_t n_chunks, const RowTask *rows,
-                       int64_t n_tasks, const int32_t *idx, const uint8_t *val, const float *wts,
+hipError_t launch_rows(int dp, const WorkItem *items, const RowTask *rows, int64_t n_tasks,
+                       const int32_t *idx, const uint8_t *val, const float *wts,
                        const float *Fp, int64_t n_fixed, float *ws, int D, float lam, float *X,
                        double *sse, int32_t *flag, double *cyc_gram, double *cyc_solve,
                        const RowPrior &pr, const Hadamard &hd, hipStream_t s);
@@ -134,9 +142,9 @@ inline int lane_width(int D) { return D <= 16 ? 16 : (D <= 20 ? 20 : 0); }
 constexpr int ne_floats(int ld) { return ((ld * (ld + 1) / 2 + ld) + 3) / 4 * 4; }
 
 // Gram of rows or chunks packed into normal-equation records (lanesolve.hip):
-// items [0, n_chunk_items) write to ws at their slot, the rest to ne at their slot.
-hipError_t launch_gram_ne(int D, const WorkItem *items, int64_t n_items, int64_t n_chunk_items,
-                          const int32_t *idx, const uint8_t *val, const float *wts,
+// chunks write to ws at their slot, whole rows to ne at their record.
+hipError_t launch_gram_ne(int D, const WorkItem *items, int64_t n_items, const int32_t *idx,
+                          const uint8_t *val, const float *wts,
                           const float *Fp, int64_t n_fixed, const float *Xold, float *ws,
                           float *ne, double *sse, const Hadamard &hd, hipStream_t s);
 

@@ -63,8 +63,8 @@ __constant__ RecordMap20 kRecordMap20 = make_record_map20();
 
 template <int DP, int LD, bool AUG, bool WT, bool TS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TS ? 4 : WT ? 5 : 6)))
-void k_gram_ne(const WorkItem *__restrict__ items, int64_t n_chunk_items,
-               const int32_t *__restrict__ idx, const uint8_t *__restrict__ val,
+void k_gram_ne(const WorkItem *__restrict__ items, const int32_t *__restrict__ idx,
+               const uint8_t *__restrict__ val,
                const float *__restrict__ wts, const float *__restrict__ Fp, int zrow,
                const float *__restrict__ Xold, int D, float *__restrict__ ws,
                float *__restrict__ ne, double *__restrict__ sse_out, Hadamard hd) {
@@ -126,7 +126,7 @@ void k_gram_ne(const WorkItem *__restrict__ items, int64_t n_chunk_items,
     }
   }
   sse = sum_wave_f64(sse);
-  float *__restrict__ out = ((int64_t)blockIdx.x < n_chunk_items ? ws : ne) + it.slot * NES;
+  float *__restrict__ out = it.slot >= 0 ? ws + it.slot * NES : ne + ~it.slot * NES;
   if constexpr (CORNER && !TS) {
     // The record is assembled in LDS (the staging area is free once the accumulation has
     // ended) with unmasked stores of each lane's values, then written with one coalesced
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 }
 
 template <int DP, int LD, bool AUG>
-static hipError_t launch_gram_ne_t(const WorkItem *items, int64_t n_items, int64_t n_chunk_items,
+static hipError_t launch_gram_ne_t(const WorkItem *items, int64_t n_items,
                                    const int32_t *idx, const uint8_t *val, const float *wts,
                                    const float *Fp, int zrow, const float *Xold, int D, float *ws,
                                    float *ne, double *sse, const Hadamard &hd, hipStream_t s) {
@@ -406,20 +406,20 @@ static hipError_t launch_gram_ne_t(const WorkItem *items, int64_t n_items, int64
     // tensor ALS has no per-rating weights
     if (wts) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_gram_ne<DP, LD, AUG, false, true>), dim3((unsigned)n_items), dim3(64),
-                       0, s, items, n_chunk_items, idx, val, wts, Fp, zrow, Xold, D, ws, ne, sse,
+                       0, s, items, idx, val, wts, Fp, zrow, Xold, D, ws, ne, sse,
                        hd);
   } else if (wts)
     hipLaunchKernelGGL((k_gram_ne<DP, LD, AUG, true, false>), dim3((unsigned)n_items), dim3(64),
-                       0, s, items, n_chunk_items, idx, val, wts, Fp, zrow, Xold, D, ws, ne, sse,
+                       0, s, items, idx, val, wts, Fp, zrow, Xold, D, ws, ne, sse,
                        hd);
   else
     hipLaunchKernelGGL((k_gram_ne<DP, LD, AUG, false, false>), dim3((unsigned)n_items), dim3(64),
-                       0, s, items, n_chunk_items, idx, val, wts, Fp, zrow, Xold, D, ws, ne, sse,
+                       0, s, items, idx, val, wts, Fp, zrow, Xold, D, ws, ne, sse,
                        hd);
   return hipSuccess;
 }
 
-hipError_t launch_gram_ne(int D, const WorkItem *items, int64_t n_items, int64_t n_chunk_items,
+hipError_t launch_gram_ne(int D, const WorkItem *items, int64_t n_items,
                           const int32_t *idx, const uint8_t *val, const float *wts,
                           const float *Fp, int64_t n_fixed, const float *Xold, float *ws,
                           float *ne, double *sse, const Hadamard &hd, hipStream_t s) {
@@ -428,10 +428,10 @@ hipError_t launch_gram_ne(int D, const WorkItem *items, int64_t n_items, int64_t
   const int ld = lane_width(D);
   hipError_t e;
   if (ld == 16)
-    e = launch_gram_ne_t<16, 16, false>(items, n_items, n_chunk_items, idx, val, wts, Fp, zrow,
+    e = launch_gram_ne_t<16, 16, false>(items, n_items, idx, val, wts, Fp, zrow,
                                         Xold, D, ws, ne, sse, hd, s);
   else if (ld == 20)
-    e = launch_gram_ne_t<32, 20, true>(items, n_items, n_chunk_items, idx, val, wts, Fp, zrow,
+    e = launch_gram_ne_t<32, 20, true>(items, n_items, idx, val, wts, Fp, zrow,
                                        Xold, D, ws, ne, sse, hd, s);
   else
     return hipErrorInvalidValue;

@@ -156,9 +156,9 @@ constexpr int kRowWaves = BAYES && !AUG              ? 2
 // the image is scaled per row and a per-row right-hand side h0 is added (RowPrior).
 //
 // The wave's task is one of three. With items (the first launch of a batch): a chunk of a
-// split row, whose normal equations go to its workspace slot and end there (the first
-// n_chunks items), or a whole row. Without items (the second launch): a split row, whose
-// summed chunks are in its first slot. Chunks share the launch of the whole rows so that
+// split row, whose normal equations go to its workspace slot and end there, or a whole row
+// (its slot is below zero). Without items (the second launch): a split row, whose summed
+// chunks are in its first slot. Chunks share the launch of the whole rows so that
 // neither leaves the chip idle at its end: as a launch of their own, few chunks kept most
 // SIMDs waiting (23 chunks of 4096 ratings at D = 50 took 182 us).
 enum TaskRole { kAnyTask, kChunkTask, kRowTask, kSplitRowTask };
@@ -184,7 +184,7 @@ struct RowLds {
 template <int DP, bool AUG, bool WT, bool BAYES, bool TS, bool STRIP, int ROLE>
 __device__ __forceinline__ void rows_task(
     char *lds,
-    const WorkItem *items, int64_t n_chunks, const RowTask *rows,
+    const WorkItem *items, const RowTask *rows,
     const int32_t *idx,
     const uint8_t *val, const float *wts,
     const float *Fp, int zrow,
@@ -205,8 +205,7 @@ __device__ __forceinline__ void rows_task(
   // one task per workgroup, whose record is then held in scalar registers
   const int64_t task = blockIdx.x;
   const bool summed = ROLE == kAnyTask ? items == nullptr : ROLE == kSplitRowTask;
-  const bool chunk = ROLE == kAnyTask ? task < n_chunks : ROLE == kChunkTask;
-  int64_t start = 0, slot;
+  int64_t start = 0, slot = 0;
   int32_t row, deg;
   if (summed) {
     const RowTask rt = rows[task];
@@ -220,6 +219,7 @@ __device__ __forceinline__ void rows_task(
     row = it.row;
     deg = it.len;
   }
+  const bool chunk = ROLE == kAnyTask ? !summed && slot >= 0 : ROLE == kChunkTask;
   const int lane = threadIdx.x & 63, kq = lane >> 4, c = lane & 15;
   const int aug_c = AUG ? aug_column<DP>(D) : -1;
 
@@ -674,7 +674,7 @@ constexpr bool kRolesApart = BAYES && !AUG && DP >= 112;
 
 template <int DP, bool AUG, bool WT, bool BAYES, bool TS, bool STRIP = false>
 __global__ __launch_bounds__(64, (kRowWaves<DP, AUG, BAYES>)) void k_rows(
-    const WorkItem *__restrict__ items, int64_t n_chunks, const RowTask *__restrict__ rows,
+    const WorkItem *__restrict__ items, const RowTask *__restrict__ rows,
     const int32_t *__restrict__ idx,
     const uint8_t *__restrict__ val, const float *__restrict__ wts,
     const float *__restrict__ Fp, int zrow,
@@ -685,14 +685,14 @@ __global__ __launch_bounds__(64, (kRowWaves<DP, AUG, BAYES>)) void k_rows(
   __shared__ __attribute__((aligned(16))) char lds[RowLds<DP, WT, TS>::kBytes];
   auto task = [&](auto role) {
     rows_task<DP, AUG, WT, BAYES, TS, STRIP, decltype(role)::value>(
-        lds, items, n_chunks, rows, idx, val, wts, Fp, zrow, ws, D, lam, X_io, sse_out,
+        lds, items, rows, idx, val, wts, Fp, zrow, ws, D, lam, X_io, sse_out,
         flag_count, cyc_gram, cyc_solve, pr, hd);
   };
   if constexpr (!kRolesApart<DP, AUG, BAYES>) {
     task(IntC<kAnyTask>{});
   } else if (items == nullptr) {
     task(IntC<kSplitRowTask>{});
-  } else if ((int64_t)blockIdx.x < n_chunks) {
+  } else if (items[blockIdx.x].slot >= 0) {
     task(IntC<kChunkTask>{});
   } else {
     task(IntC<kRowTask>{});
@@ -705,14 +705,13 @@ static constexpr bool has_aug(int D) {
 }
 
 template <int DP, bool AUG, bool WT, bool BAYES, bool TS = false, bool STRIP = false>
-static void launch_rows_k(const WorkItem *items, int64_t n_chunks,
-                          const RowTask *rows, int64_t n_tasks,
+static void launch_rows_k(const WorkItem *items, const RowTask *rows, int64_t n_tasks,
                           const int32_t *idx, const uint8_t *val, const float *wts,
                           const float *Fp, int zrow, float *ws, int D, float lam, float *X,
                           double *sse, int32_t *flag, double *cyc_gram, double *cyc_solve,
                           const RowPrior &pr, const Hadamard &hd, hipStream_t s) {
   hipLaunchKernelGGL((k_rows<DP, AUG, WT, BAYES, TS, STRIP>), dim3((unsigned)n_tasks),
-                     dim3(64), 0, s, items, n_chunks, rows, idx, val, wts, Fp,
+                     dim3(64), 0, s, items, rows, idx, val, wts, Fp,
                      zrow, ws, D,
                      lam, X, sse, flag, cyc_gram, cyc_solve, pr, hd);
 }
@@ -727,7 +726,7 @@ static void launch_rows_aug(bool strip, A &&...args) {
 }
 
 template <int DP>
-static hipError_t launch_rows_t(const WorkItem *items, int64_t n_chunks, const RowTask *rows,
+static hipError_t launch_rows_t(const WorkItem *items, const RowTask *rows,
                                 int64_t n_tasks, const int32_t *idx,
                                 const uint8_t *val, const float *wts, const float *Fp, int zrow,
                                 float *ws, int D, float lam, float *X, double *sse,
@@ -735,7 +734,7 @@ static hipError_t launch_rows_t(const WorkItem *items, int64_t n_chunks, const R
                                 const RowPrior &pr, const Hadamard &hd, hipStream_t s) {
   if (n_tasks <= 0) return hipSuccess;
   const bool aug = has_aug<DP>(D), wt = wts != nullptr, strip = strip_width<DP>(D);
-#define ROW_ARGS items, n_chunks, rows, n_tasks, idx, val, wts, Fp, zrow, ws, D, lam, X, sse, flag, \
+#define ROW_ARGS items, rows, n_tasks, idx, val, wts, Fp, zrow, ws, D, lam, X, sse, flag, \
                  cyc_gram, cyc_solve, pr, hd, s
   if (hd.idx2) {
     // tensor ALS (and its Gibbs draws): no weights; the tile form throughout (with the
@@ -782,16 +781,16 @@ static hipError_t launch_rows_t(const WorkItem *items, int64_t n_chunks, const R
     default: return hipErrorInvalidValue;       \
   }
 
-hipError_t launch_rows(int dp, const WorkItem *items, int64_t n_chunks, const RowTask *rows,
+hipError_t launch_rows(int dp, const WorkItem *items, const RowTask *rows,
                        int64_t n_tasks, const int32_t *idx, const uint8_t *val, const float *wts,
                        const float *Fp, int64_t n_fixed, float *ws, int D, float lam, float *X,
                        double *sse, int32_t *flag, double *cyc_gram, double *cyc_solve,
                        const RowPrior &pr, const Hadamard &hd, hipStream_t s) {
   if ((cyc_gram == nullptr) != (cyc_solve == nullptr)) return hipErrorInvalidValue;
-  if ((items == nullptr) == (rows == nullptr) || (rows && n_chunks != 0))
+  if ((items == nullptr) == (rows == nullptr))
     return hipErrorInvalidValue;
   const int zrow = (int)n_fixed;
-  ALS_DP_SWITCH(dp, return launch_rows_t<DPV>(items, n_chunks, rows, n_tasks, idx, val, wts, Fp,
+  ALS_DP_SWITCH(dp, return launch_rows_t<DPV>(items, rows, n_tasks, idx, val, wts, Fp,
                                               zrow, ws, D, lam, X, sse, flag, cyc_gram, cyc_solve,
                                               pr, hd, s));
 }

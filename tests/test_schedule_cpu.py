@@ -1,0 +1,37 @@
+"""The order in which a half-sweep's gather items start, on the host alone."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_1108_2580_amd as pkg
+
+ITEM = np.dtype([("start", "<i8"), ("slot", "<i8"), ("len", "<i4"), ("row", "<i4")])
+
+
+def order_items(items, n_chunks):
+    fn = ctypes.CDLL(pkg.LIB_PATH)._ZN3als11order_itemsEPNS_8WorkItemEll
+    fn.restype = ctypes.c_int64
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64]
+    out = items.copy()
+    return fn(out.ctypes.data, n_chunks, len(out)), out
+
+
+@pytest.mark.parametrize("chunk_lens,row_lens", [
+    ([], [9, 5, 1]), ([4, 4, 2], []), ([4, 4, 2], [8, 6, 5, 4, 3, 1]), ([4, 3], [4, 2]),
+    ([256] * 9, [500, 257, 256, 0]), ([1], [3, 2, 1])])
+def test_largest_work_starts_first(chunk_lens, row_lens):
+    n = len(chunk_lens)
+    items = np.zeros(n + len(row_lens), ITEM)
+    items["len"] = chunk_lens + row_lens
+    items["slot"] = list(range(n)) + [~k for k in range(len(row_lens))]
+    items["start"] = np.arange(len(items)) * 1000
+    lead, out = order_items(items, n)
+    assert sorted(map(tuple, out)) == sorted(map(tuple, items))
+    whole = out["slot"] < 0
+    longest = max(chunk_lens, default=0)
+    assert lead == (sum(k > longest for k in row_lens) if n else 0)
+    assert whole[:lead].all() and not whole[lead:lead + n].any() and whole[lead + n:].all()
+    # no whole row longer than the chunks is left behind them, and the rows keep their order
+    assert (out["len"][lead + n:] <= longest).all() or not n
+    assert out["len"][whole].tolist() == row_lens
