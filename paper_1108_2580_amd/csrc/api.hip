@@ -27,7 +27,15 @@ using als::WorkItem;
 
 namespace als {
 
-int64_t order_items(WorkItem *items, int64_t n_chunks, int64_t n) {
+int64_t even_chunk(int64_t d, int64_t chunk) {
+  const int64_t n = (d + chunk - 1) / chunk;
+  return ((d + n - 1) / n + 63) / 64 * 64;
+}
+
+int64_t order_items(WorkItem *items, const int64_t *ptr, int64_t n_chunks, int64_t n) {
+  std::stable_sort(items, items + n_chunks, [&](const WorkItem &x, const WorkItem &y) {
+    return x.start - ptr[x.row] < y.start - ptr[y.row];
+  });
   int32_t longest = 0;
   for (int64_t i = 0; i < n_chunks; ++i) longest = std::max(longest, items[i].len);
   int64_t lead = 0;
@@ -279,8 +287,9 @@ void auto_split(const als_ctx *ctx, int64_t ratings, int64_t &hub, int64_t &chun
 // (7102, 7118): their chunks' records cost what the hits save.
 struct Split {
   int64_t hub = 0, chunk = 0, windows = 1;
+  bool even = false;  // cut into pieces of one length (automatic splits)
   int64_t chunk_of(int64_t d) const {
-    if (windows <= 1) return chunk;
+    if (windows <= 1) return even ? als::even_chunk(d, chunk) : chunk;
     return std::min(chunk, std::max<int64_t>(kMinWindowChunk, (d / windows + 63) / 64 * 64));
   }
   int64_t chunks_of(int64_t d) const {
@@ -324,6 +333,7 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
   sp.chunk = ctx->tune.chunk;
   if (!sp.hub && !sp.chunk) {
     auto_split(ctx, ratings, sp.hub, sp.chunk);
+    sp.even = true;
     if (ctx->lane_solve) {
       sp.windows = n_fixed * ctx->DP * 4 / kWindowBytes;
       if (sp.windows < kMinWindows) sp.windows = 1;
@@ -401,8 +411,8 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
       P.gitems.push_back(it);
     }
     b.n_gitems = (int64_t)P.gitems.size() - b.gitem_off;
-    b.chunk_off = b.gitem_off + als::order_items(P.gitems.data() + b.gitem_off, b.n_gchunks,
-                                                 b.n_gitems);
+    b.chunk_off = b.gitem_off + als::order_items(P.gitems.data() + b.gitem_off, ptr.data(),
+                                                 b.n_gchunks, b.n_gitems);
     b.n_rows = (int64_t)P.rows.size() - b.row_off;
     P.n_chunks += b.n_gchunks;
     P.batches.push_back(b);

@@ -18,13 +18,21 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 24, "WorkItem layout");
 
+// Ratings per chunk of a row of d ratings cut into as many chunks as chunk (a multiple of 64)
+// asks for, but of one length, rounded up to 64 (api.hip).
+int64_t even_chunk(int64_t d, int64_t chunk);
 // Order of a batch's items (api.hip): given its chunks and then its whole rows by descending
 // length, the rows longer than every chunk move ahead of the chunks, so that the largest work
 // starts first; returns their number. Behind the chunks, a few rows just under the splitting
 // threshold ran on alone at the end (2500 rows of about 4000 ratings, nine of them whole, D =
 // 33: 457 us a half-sweep behind, 412 ahead; of about 1200, 153 and 132; time bins of 3300
 // ratings, D = 10, 178 and 160; 1500 rows of 3300, D = 100, 856 and 774).
-int64_t order_items(WorkItem *items, int64_t n_chunks, int64_t n);
+// Chunks go by their depth in their row, so that those in flight read one part of the fixed
+// table, as whole rows walking it side by side do; row by row they spread over all of it. With
+// even_chunk, us a half-sweep row by row and by depth: 4000 rows of 750 ratings, D = 10 60 and
+// 48, D = 20 78 and 67; 1500 time bins of 6700, D = 10, 167 and 141; 4500 of 2200 191 and 161;
+// 2500 rows of 4000, D = 33, 412 and 375; 1000 of 5000, D = 100, 773 and 628.
+int64_t order_items(WorkItem *items, const int64_t *ptr, int64_t n_chunks, int64_t n);
 
 // One row to solve, from its record (narrow widths) or its workspace slots (split rows).
 struct RowTask {

@@ -9,12 +9,18 @@ import paper_1108_2580_amd as pkg
 ITEM = np.dtype([("start", "<i8"), ("slot", "<i8"), ("len", "<i4"), ("row", "<i4")])
 
 
-def order_items(items, n_chunks):
-    fn = ctypes.CDLL(pkg.LIB_PATH)._ZN3als11order_itemsEPNS_8WorkItemEll
+def library(name, *argtypes):
+    fn = getattr(ctypes.CDLL(pkg.LIB_PATH), name)
     fn.restype = ctypes.c_int64
-    fn.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64]
+    fn.argtypes = argtypes
+    return fn
+
+
+def order_items(items, ptr, n_chunks):
+    fn = library("_ZN3als11order_itemsEPNS_8WorkItemEPKlll", ctypes.c_void_p, ctypes.c_void_p,
+                 ctypes.c_int64, ctypes.c_int64)
     out = items.copy()
-    return fn(out.ctypes.data, n_chunks, len(out)), out
+    return fn(out.ctypes.data, ptr.ctypes.data, n_chunks, len(out)), out
 
 
 @pytest.mark.parametrize("chunk_lens,row_lens", [
@@ -25,8 +31,9 @@ def test_largest_work_starts_first(chunk_lens, row_lens):
     items = np.zeros(n + len(row_lens), ITEM)
     items["len"] = chunk_lens + row_lens
     items["slot"] = list(range(n)) + [~k for k in range(len(row_lens))]
+    items["row"] = np.arange(len(items))
     items["start"] = np.arange(len(items)) * 1000
-    lead, out = order_items(items, n)
+    lead, out = order_items(items, items["start"].astype(np.int64), n)
     assert sorted(map(tuple, out)) == sorted(map(tuple, items))
     whole = out["slot"] < 0
     longest = max(chunk_lens, default=0)
@@ -35,3 +42,23 @@ def test_largest_work_starts_first(chunk_lens, row_lens):
     # no whole row longer than the chunks is left behind them, and the rows keep their order
     assert (out["len"][lead + n:] <= longest).all() or not n
     assert out["len"][whole].tolist() == row_lens
+
+
+@pytest.mark.parametrize("degrees,chunk", [([700], 256), ([3000, 2100, 600, 513], 256),
+                                           ([9001, 8193, 8193], 4096), ([1153] * 7, 576)])
+def test_chunks_are_even_and_go_by_depth(degrees, chunk):
+    even = library("_ZN3als10even_chunkEll", ctypes.c_int64, ctypes.c_int64)
+    ptr = np.concatenate([[0], np.cumsum(degrees)]).astype(np.int64)
+    items = []
+    for row, d in enumerate(degrees):
+        c = even(d, chunk)
+        # as many chunks as before, none longer, each but the last of the same whole groups
+        assert c % 64 == 0 and c <= chunk and -(-d // c) == -(-d // chunk)
+        assert -(-d // c) * 64 > -(-d // c) * c - d  # the last is short by less than 64 a chunk
+        for q in range(-(-d // c)):
+            items.append((ptr[row] + q * c, len(items), min(c, d - q * c), row))
+    items = np.array(items, ITEM)
+    lead, out = order_items(items, ptr, len(items))
+    assert lead == 0 and sorted(map(tuple, out)) == sorted(map(tuple, items))
+    depth = out["start"] - ptr[out["row"]]
+    assert (np.diff(depth) >= 0).all()
