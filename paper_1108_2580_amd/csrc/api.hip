@@ -912,7 +912,7 @@ als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out
   // after it, or the phases are timed one by one
   als::SolveReduce red;
   if (ctx->lane_solve && P.batches.size() == 1 &&
-      als::solve_blocks(P.batches[0].n_rows) <= als::kSolveReduceBlocks &&
+      als::solve_reduces(P.batches[0].n_rows, (int64_t)P.gitems.size()) &&
       !(pr.init && !P.zero_rows.empty()) && !(ctx->profiling && ctx->prof_mode == 1)) {
     red.sse = ctx->d_sse_items;
     red.n = (int64_t)P.gitems.size();

@@ -171,7 +171,14 @@ struct SolveReduce {
 // that they save: 47 and 79 blocks (5000 x 3000) 133 us without and 128 with, 16 and 32 blocks
 // 53 and 46, but 782 and 1563 blocks 346 and 380, 157 and 313 blocks 127 and 142.
 constexpr int64_t kSolveReduceBlocks = 64;
+// A block's run of residuals is eight loads a lane, in flight together. Few rows of many chunks
+// leave each block thousands: 50 time bins (one block), tensor ALS at D = 10, us a half-sweep
+// with a launch of its own and in the solve: 100k ratings 23 and 24, 300k 25 and 27, 3M 57 and
+// 89, 10M 120 and 154. 500 bins (eight blocks), 1M 38 and 37, 3M 60 and 62.
+constexpr int64_t kSolveReduceRun = 64 * 8;
 inline int64_t solve_blocks(int64_t n_rows) { return (n_rows + 63) / 64; }
+// Whether the solve of n_rows rows adds up n_residuals itself.
+bool solve_reduces(int64_t n_rows, int64_t n_residuals);
 
 // One row per lane: regularise, Cholesky, solve, write (lanesolve.hip). Row i of
 // the launch uses record base + i; its first n_split rows are split rows whose

@@ -231,15 +231,14 @@ __global__ __launch_bounds__(256) void k_sum_records(const RowTask *__restrict__
 }
 
 // With red.sse the blocks also add up the entering-state squared residuals: each takes a run
-// of them while its records load, and the block that finishes last adds the runs' sums in
-// order (whichever block it is) and hands total and flag count to the host, in place of a
-// reduction launch of about 5 us.
+// of them, several loads at a time, before its records, and the block that finishes last adds
+// the runs' sums in order (whichever block it is) and hands total and flag count to the host,
+// in place of a reduction launch of about 5 us.
 template <int LD, bool BAYES>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_solve_lane(const RowTask *__restrict__ rows, int64_t n_rows,
-                                                   int64_t base, const float *__restrict__ ne,
-                                                   int D, float lam, float *__restrict__ X,
-                                                   int32_t *flag_count, RowPrior pr,
-                                                   SolveReduce red) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+void k_solve_lane(const RowTask *__restrict__ rows, int64_t n_rows, int64_t base,
+                  const float *__restrict__ ne, int D, float lam, float *__restrict__ X,
+                  int32_t *flag_count, RowPrior pr, SolveReduce red) {
   constexpr int NTRI = LD * (LD + 1) / 2;
   constexpr int NES = ne_floats(LD);
   constexpr int NQ = NES / 4;               // float4 of a record
@@ -256,6 +255,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     const int64_t per = (red.n + gridDim.x - 1) / gridDim.x;
     const int64_t end = min((blockIdx.x + 1) * per, red.n);
     double t = 0.0;
+#pragma unroll 8
     for (int64_t k = blockIdx.x * per + lane; k < end; k += 64) t += red.sse[k];
     t = sum_wave_f64(t);
     if (lane == 0)
@@ -451,12 +451,17 @@ static void launch_solve_lane_t(unsigned blocks, const RowTask *rows, int64_t n_
                        base, ne, D, lam, X, flag, pr, red);
 }
 
+bool solve_reduces(int64_t n_rows, int64_t n_residuals) {
+  const int64_t blocks = solve_blocks(n_rows);
+  return blocks <= kSolveReduceBlocks && n_residuals <= blocks * kSolveReduceRun;
+}
+
 hipError_t launch_solve_lane(int D, const RowTask *rows, int64_t n_rows, int64_t n_split,
                              int64_t base, const float *ws, float *ne, float lam, float *X,
                              int32_t *flag, const RowPrior &pr, const SolveReduce &red,
                              hipStream_t s) {
   if (n_rows <= 0) return hipSuccess;
-  if (red.sse && solve_blocks(n_rows) > kSolveReduceBlocks) return hipErrorInvalidValue;
+  if (red.sse && !solve_reduces(n_rows, red.n)) return hipErrorInvalidValue;
   const int ld = lane_width(D);
   if (ld != 16 && ld != 20) return hipErrorInvalidValue;
   if (n_split > 0) {

@@ -62,3 +62,12 @@ def test_chunks_are_even_and_go_by_depth(degrees, chunk):
     assert lead == 0 and sorted(map(tuple, out)) == sorted(map(tuple, items))
     depth = out["start"] - ptr[out["row"]]
     assert (np.diff(depth) >= 0).all()
+
+
+@pytest.mark.parametrize("rows,residuals,fused", [
+    (1, 512, True), (50, 513, False), (50, 10_000, False), (64, 512, True), (65, 1024, True),
+    (65, 1025, False), (4096, 64 * 512, True), (4096, 64 * 512 + 1, False), (4097, 4097, False)])
+def test_the_solve_adds_up_bounded_runs_of_residuals(rows, residuals, fused):
+    fn = library("_ZN3als13solve_reducesEll", ctypes.c_int64, ctypes.c_int64)
+    fn.restype = ctypes.c_bool
+    assert fn(rows, residuals) == fused
