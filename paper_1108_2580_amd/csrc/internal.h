@@ -8,6 +8,10 @@
 
 namespace als {
 
+// Blocks of one launch at most: HIP refuses a grid of 2^32 threads and more. Launches that can
+// need more go in slices.
+constexpr int64_t max_blocks(int threads) { return 0xffffffffLL / threads; }
+
 // One unit of Gram work: a whole row, or one chunk of a split ("hub") row.
 struct WorkItem {
   int64_t start;  // first rating of the item, offset into the side's idx/val arrays

@@ -802,10 +802,15 @@ hipError_t launch_sum_slots(int dp, int D, const RowTask *rows, int64_t n_split,
   const bool aug = ((D + 3) & ~3) < dp;
   const int nq = (num_tiles(dp) * 256 + (aug ? 0 : dp)) / 4;
   const int parts = (nq + 63) / 64;
-  if (n_split * parts > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_sum_slots, dim3((unsigned)(n_split * parts)), dim3(256), 0, s, rows,
-                     dp / 16, D, nq, parts, lam, ws, pr);
-  return hipGetLastError();
+  const int64_t per = max_blocks(256) / parts;  // rows of a launch
+  for (int64_t first = 0; first < n_split; first += per) {
+    const int64_t n = std::min(per, n_split - first);
+    hipLaunchKernelGGL(k_sum_slots, dim3((unsigned)(n * parts)), dim3(256), 0, s, rows + first,
+                       dp / 16, D, nq, parts, lam, ws, pr);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace als

@@ -1,0 +1,56 @@
+"""Launches of more threads than one HIP grid holds (2^32 - 1) go in slices that cover the work
+once. No GPU: a stand-in for HIP's launch calls records what the library would launch."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+import paper_1108_2580_amd as pkg
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIMIT = 2 ** 32
+
+CALL = """
+import ctypes, sys
+ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+fn = getattr(ctypes.CDLL(sys.argv[2]), sys.argv[3])
+types = dict(i=ctypes.c_int, l=ctypes.c_int64, f=ctypes.c_float, p=ctypes.c_void_p)
+empty = ctypes.create_string_buffer(256)  # a zeroed RowPrior or Hadamard
+args = [a.split(":") for a in sys.argv[4:]]
+fn.argtypes = [types[t[0]] for t, _ in args]
+sys.exit(fn(*[ctypes.addressof(empty) if v == "empty" else float(v) if t == "f" else int(v)
+              for t, v in args]))
+"""
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("recorder") / "librecorder.so")
+    subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", "-o", lib,
+                           os.path.join(HERE, "launch_recorder.c")])
+
+    def run(name, n_args, *args):
+        r = subprocess.run([sys.executable, "-c", CALL, lib, pkg.LIB_PATH, name, *args],
+                           capture_output=True, text=True,
+                           env=dict(os.environ, RECORDED_ARGS=str(n_args)))
+        assert r.returncode == 0, r.stderr
+        out = [[int(w) for w in line.split()] for line in r.stdout.splitlines()]
+        assert all(threads * blocks < LIMIT for threads, blocks, *_ in out)
+        return out
+
+    return run
+
+
+# rows of two chunks each; at D = 100 a split row's sum takes 28 blocks of 256 threads
+@pytest.mark.parametrize("D,DP,parts", [(100, 112, 28), (128, 128, 37), (33, 48, 6)])
+@pytest.mark.parametrize("n", [1000, 600_000, 5_600_000])
+def test_sums_of_split_rows(launches, D, DP, parts, n):
+    out = launches("_ZN3als16launch_sum_slotsEiiPKNS_7RowTaskElfPfRKNS_8RowPriorEP12ihipStream_t", 1,
+                   f"i:{DP}", f"i:{D}", "p:4096", f"l:{n}", "f:0.1", "p:8192", "p:empty", "p:0")
+    assert len(out) == -(-n // ((LIMIT - 1) // 256 // parts))
+    at = 4096  # RowTask records of 24 bytes
+    for threads, blocks, rows, *_ in out:
+        assert threads == 256 and blocks % parts == 0 and rows == at
+        at += blocks // parts * 24
+    assert at == 4096 + 24 * n
