@@ -478,8 +478,8 @@ als_status order_chunks(als_ctx *ctx, SidePlan &P, const int32_t *d_idx, int64_t
 // Tasks of the fused row kernel in one half-sweep: the gather items, then the split rows.
 int64_t cycle_tasks(const SidePlan &P) { return (int64_t)P.gitems.size() + P.split_rows; }
 
-// pairs of one predict call: the launch has pair_blocks(n, D) < 2^31 blocks (with up to 8
-// lanes per pair)
+// pairs of one call, as documented: pair_blocks(n, D) stays below 2^31 with up to 8 lanes per
+// pair (more than one grid's threads go in several launches)
 constexpr int64_t kMaxPairs = 0x7fffffffLL * 256 / 8;
 
 void free_holdout(als_ctx *c) {

@@ -13,6 +13,8 @@
 // indices fall outside the factor tables give NaN and read nothing. With
 // ratings, each 256-lane block writes the fp64 sum of its pairs' squared
 // errors; a fixed-order reduction follows, so the sum is reproducible.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace als {
@@ -225,11 +227,22 @@ hipError_t launch_predict(const float *U, const float *V, int64_t M, int64_t N, 
                           const int32_t *users, const int32_t *items, const uint8_t *r,
                           float *pred, double *sse_blocks, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  if (pair_blocks(n, D) > 0x7fffffff || (sse_blocks && !r)) return hipErrorInvalidValue;
-  const int vw = predict_vec(D);
-  if (vw == 4) return launch_predict_vw<4>(U, V, M, N, D, n, users, items, r, pred, sse_blocks, s);
-  if (vw == 2) return launch_predict_vw<2>(U, V, M, N, D, n, users, items, r, pred, sse_blocks, s);
-  return launch_predict_vw<1>(U, V, M, N, D, n, users, items, r, pred, sse_blocks, s);
+  if (sse_blocks && !r) return hipErrorInvalidValue;
+  const int vw = predict_vec(D), G = predict_group(D);
+  const int64_t blocks = max_blocks(kPairBlock), per = blocks * kPairBlock / G;  // a launch's
+  for (int64_t first = 0; first < n; first += per) {
+    const int64_t k = std::min(per, n - first);
+    const uint8_t *rk = r ? r + first : nullptr;
+    float *pk = pred ? pred + first : nullptr;
+    double *sk = sse_blocks ? sse_blocks + first / per * blocks : nullptr;
+    const auto launch = vw == 4   ? launch_predict_vw<4>
+                        : vw == 2 ? launch_predict_vw<2>
+                                  : launch_predict_vw<1>;
+    const hipError_t e =
+        launch(U, V, M, N, D, k, users + first, items + first, rk, pk, sk, s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace als

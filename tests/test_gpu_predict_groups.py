@@ -38,3 +38,19 @@ def test_group_edges(D):
             rmse = als.holdout_rmse(dev_f(U), dev_f(V))
             assert abs(rmse - np.sqrt(np.mean((r - want) ** 2))) <= min(
                 RMSE_TOL, np.sqrt(np.mean(bound ** 2)) + 1e-12)
+
+
+def test_more_pairs_than_one_grid():
+    """Eight lanes per pair: 2^32 threads are passed at 537M pairs, which repeat every 4096."""
+    M, N, D, n = 301, 203, 50, 2 ** 29 + 8192
+    rng = np.random.default_rng(D)
+    U = rng.standard_normal((M, D), dtype=np.float32)
+    V = rng.standard_normal((N, D), dtype=np.float32)
+    users = dev_i(rng.integers(0, M, 4096).astype(np.int32)).repeat(n // 4096)
+    items = dev_i(rng.integers(0, N, 4096).astype(np.int32)).repeat(n // 4096)
+    print(f"predict D={D} pairs={n}", flush=True)
+    with small_ctx(M, N, D) as als:
+        got = als.predict(dev_f(U), dev_f(V), users, items).view(-1, 4096)
+        assert torch.equal(got, got[:1].expand_as(got))
+        one = als.predict(dev_f(U), dev_f(V), users[:4096].clone(), items[:4096].clone())
+        assert torch.equal(one, got[-1])

@@ -54,3 +54,22 @@ def test_sums_of_split_rows(launches, D, DP, parts, n):
         assert threads == 256 and blocks % parts == 0 and rows == at
         at += blocks // parts * 24
     assert at == 4096 + 24 * n
+
+
+# one, four and eight lanes per pair, with float, float2 and float4 loads
+@pytest.mark.parametrize("D,lanes", [(3, 1), (10, 4), (50, 8), (33, 8), (20, 4), (100, 8)])
+@pytest.mark.parametrize("n", [1000, 600_000_000, 5_000_000_000])
+@pytest.mark.parametrize("sse", [False, True])
+def test_predictions(launches, D, lanes, n, sse):
+    pred, r, blocks_out = (0, 1 << 36, 1 << 37) if sse else (1 << 35, 0, 0)
+    out = launches("_ZN3als14launch_predictEPKfS1_llilPKiS3_PKhPfPdP12ihipStream_t", 11,
+                   "p:4096", "p:8192", "l:1000", "l:900", f"i:{D}", f"l:{n}", f"p:{1 << 33}",
+                   f"p:{1 << 34}", f"p:{r}", f"p:{pred}", f"p:{blocks_out}", "p:0")
+    first = block = 0
+    for threads, blocks, U, V, M, N, _, k, users, items, rk, pk, bk in out:
+        assert threads == 256 and blocks == -(-k * lanes // 256)
+        assert (users, items) == ((1 << 33) + 4 * first, (1 << 34) + 4 * first)
+        assert (rk, pk) == ((r + first, 0) if sse else (0, pred + 4 * first))
+        assert bk == (blocks_out + 8 * block if sse else 0)
+        first, block = first + k, block + blocks
+    assert first == n and block == -(-n * lanes // 256)
