@@ -22,6 +22,8 @@
 //                rows it also reduces the squared residuals.
 // Records hold LD(LD+1)/2 + LD floats (LD = 16 or 20, the width the solve is
 // compiled for; padded features solve to zero), rounded up to a multiple of 4.
+#include <algorithm>
+
 #include "gram.h"
 
 namespace als {
@@ -402,20 +404,14 @@ static hipError_t launch_gram_ne_t(const WorkItem *items, int64_t n_items,
                                    const int32_t *idx, const uint8_t *val, const float *wts,
                                    const float *Fp, int zrow, const float *Xold, int D, float *ws,
                                    float *ne, double *sse, const Hadamard &hd, hipStream_t s) {
-  if (hd.idx2) {
-    // tensor ALS has no per-rating weights
-    if (wts) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_gram_ne<DP, LD, AUG, false, true>), dim3((unsigned)n_items), dim3(64),
-                       0, s, items, idx, val, wts, Fp, zrow, Xold, D, ws, ne, sse,
-                       hd);
-  } else if (wts)
-    hipLaunchKernelGGL((k_gram_ne<DP, LD, AUG, true, false>), dim3((unsigned)n_items), dim3(64),
-                       0, s, items, idx, val, wts, Fp, zrow, Xold, D, ws, ne, sse,
-                       hd);
-  else
-    hipLaunchKernelGGL((k_gram_ne<DP, LD, AUG, false, false>), dim3((unsigned)n_items), dim3(64),
-                       0, s, items, idx, val, wts, Fp, zrow, Xold, D, ws, ne, sse,
-                       hd);
+  if (hd.idx2 && wts) return hipErrorInvalidValue;  // tensor ALS has no per-rating weights
+  const auto kernel = hd.idx2 ? k_gram_ne<DP, LD, AUG, false, true>
+                      : wts   ? k_gram_ne<DP, LD, AUG, true, false>
+                              : k_gram_ne<DP, LD, AUG, false, false>;
+  constexpr int64_t per = max_blocks(64);
+  for (int64_t first = 0; first < n_items; first += per)
+    hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(per, n_items - first)), dim3(64), 0, s,
+                       items + first, idx, val, wts, Fp, zrow, Xold, D, ws, ne, sse + first, hd);
   return hipSuccess;
 }
 
@@ -465,12 +461,11 @@ hipError_t launch_solve_lane(int D, const RowTask *rows, int64_t n_rows, int64_t
   const int ld = lane_width(D);
   if (ld != 16 && ld != 20) return hipErrorInvalidValue;
   if (n_split > 0) {
-    if (ld == 16)
-      hipLaunchKernelGGL(k_sum_records<16>, dim3((unsigned)n_split), dim3(256), 0, s, rows, base,
-                         ws, ne);
-    else
-      hipLaunchKernelGGL(k_sum_records<20>, dim3((unsigned)n_split), dim3(256), 0, s, rows, base,
-                         ws, ne);
+    constexpr int64_t per = max_blocks(256);
+    for (int64_t first = 0; first < n_split; first += per)
+      hipLaunchKernelGGL(ld == 16 ? k_sum_records<16> : k_sum_records<20>,
+                         dim3((unsigned)std::min(per, n_split - first)), dim3(256), 0, s,
+                         rows + first, base + first, ws, ne);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -13,6 +13,8 @@
 // The wavefront total goes to sse_items[item]; a fixed-order reduction over the items
 // follows. TS (tensor ALS): f is the elementwise product of the staged rows Fp[j] and
 // hd.Tp[t], t the rating's second index.
+#include <algorithm>
+
 #include "gram.h"
 
 namespace als {
@@ -67,12 +69,11 @@ static hipError_t launch_resid_t(const WorkItem *items, int64_t n_items, const i
                                  const uint8_t *val, const float *Fp, int zrow, const float *X,
                                  int D, double *sse_items, const Hadamard &hd, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  if (hd.idx2)
-    hipLaunchKernelGGL((k_resid<DP, true>), dim3((unsigned)n_items), dim3(64), 0, s, items, idx,
-                       val, Fp, zrow, X, D, sse_items, hd);
-  else
-    hipLaunchKernelGGL((k_resid<DP, false>), dim3((unsigned)n_items), dim3(64), 0, s, items, idx,
-                       val, Fp, zrow, X, D, sse_items, hd);
+  constexpr int64_t per = max_blocks(64);
+  for (int64_t first = 0; first < n_items; first += per)
+    hipLaunchKernelGGL((hd.idx2 ? k_resid<DP, true> : k_resid<DP, false>),
+                       dim3((unsigned)std::min(per, n_items - first)), dim3(64), 0, s,
+                       items + first, idx, val, Fp, zrow, X, D, sse_items + first, hd);
   return hipGetLastError();
 }
 

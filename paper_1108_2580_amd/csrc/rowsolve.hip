@@ -710,10 +710,14 @@ static void launch_rows_k(const WorkItem *items, const RowTask *rows, int64_t n_
                           const float *Fp, int zrow, float *ws, int D, float lam, float *X,
                           double *sse, int32_t *flag, double *cyc_gram, double *cyc_solve,
                           const RowPrior &pr, const Hadamard &hd, hipStream_t s) {
-  hipLaunchKernelGGL((k_rows<DP, AUG, WT, BAYES, TS, STRIP>), dim3((unsigned)n_tasks),
-                     dim3(64), 0, s, items, rows, idx, val, wts, Fp,
-                     zrow, ws, D,
-                     lam, X, sse, flag, cyc_gram, cyc_solve, pr, hd);
+  constexpr int64_t per = max_blocks(64);
+  for (int64_t first = 0; first < n_tasks; first += per)
+    hipLaunchKernelGGL((k_rows<DP, AUG, WT, BAYES, TS, STRIP>),
+                       dim3((unsigned)std::min(per, n_tasks - first)), dim3(64), 0, s,
+                       items ? items + first : nullptr, rows ? rows + first : nullptr, idx, val,
+                       wts, Fp, zrow, ws, D, lam, X, sse + first, flag,
+                       cyc_gram ? cyc_gram + first : nullptr,
+                       cyc_solve ? cyc_solve + first : nullptr, pr, hd);
 }
 
 // The augmented variants, in strip form where the last tile uses four features.

@@ -73,3 +73,62 @@ def test_predictions(launches, D, lanes, n, sse):
         assert bk == (blocks_out + 8 * block if sse else 0)
         first, block = first + k, block + blocks
     assert first == n and block == -(-n * lanes // 256)
+
+
+ITEMS = [1000, 70_000_000, 200_000_000]
+
+
+def check_slices(out, n, at, *strides):
+    """Every launch starts where the one before ended, in each of the arrays at `at`."""
+    first = 0
+    for threads, blocks, *args in out:
+        assert threads == 64
+        for (k, base), stride in zip(at, strides):
+            assert args[k] == base + stride * first
+        first += blocks
+    assert first == n and len(out) == -(-n // ((LIMIT - 1) // 64))
+
+
+@pytest.mark.parametrize("D,DP", [(33, 48), (100, 112), (128, 128)])
+@pytest.mark.parametrize("n", ITEMS)
+@pytest.mark.parametrize("split_rows", [False, True])
+def test_rows(launches, D, DP, n, split_rows):
+    items, rows = (0, 1 << 33) if split_rows else (1 << 33, 0)
+    out = launches("_ZN3als11launch_rowsEiPKNS_8WorkItemEPKNS_7RowTaskElPKiPKhPKfSB_lPfifSC_PdPiSD"
+                   "_SD_RKNS_8RowPriorERKNS_8HadamardEP12ihipStream_t", 13,
+                   f"i:{DP}", f"p:{items}", f"p:{rows}", f"l:{n}", "p:64", "p:64", "p:0", "p:64",
+                   "l:1000", "p:64", f"i:{D}", "f:0.1", "p:64", f"p:{1 << 35}", "p:64", "p:0",
+                   "p:0", "p:empty", "p:empty", "p:0")
+    check_slices(out, n, [(split_rows, 1 << 33), (11, 1 << 35)], 24, 8)
+
+
+@pytest.mark.parametrize("D", [10, 20])
+@pytest.mark.parametrize("n", ITEMS)
+def test_narrow_grams(launches, D, n):
+    out = launches("_ZN3als14launch_gram_neEiPKNS_8WorkItemElPKiPKhPKfS8_lS8_PfS9_PdRKNS_8Hadamard"
+                   "EP12ihipStream_t", 11,
+                   f"i:{D}", f"p:{1 << 33}", f"l:{n}", "p:64", "p:64", "p:0", "p:64", "l:1000",
+                   "p:64", "p:64", "p:64", f"p:{1 << 35}", "p:empty", "p:0")
+    check_slices(out, n, [(0, 1 << 33), (10, 1 << 35)], 24, 8)
+
+
+@pytest.mark.parametrize("DP", [16, 48])
+@pytest.mark.parametrize("n", ITEMS)
+def test_residuals(launches, DP, n):
+    out = launches("_ZN3als12launch_residEiPKNS_8WorkItemElPKiPKhPKflS8_iPdRKNS_8HadamardEP12ihip"
+                   "Stream_t", 8, f"i:{DP}", f"p:{1 << 33}", f"l:{n}", "p:64", "p:64", "p:64",
+                   "l:1000", "p:64", f"i:{DP}", f"p:{1 << 35}", "p:empty", "p:0")
+    check_slices(out, n, [(0, 1 << 33), (7, 1 << 35)], 24, 8)
+
+
+@pytest.mark.parametrize("D", [10, 20])
+@pytest.mark.parametrize("n", [1000, 20_000_000])
+def test_sums_of_split_records(launches, D, n):
+    out = launches("_ZN3als17launch_solve_laneEiPKNS_7RowTaskElllPKfPffS5_PiRKNS_8RowPriorERKNS_11"
+                   "SolveReduceEP12ihipStream_t", 4, f"i:{D}", f"p:{1 << 33}", f"l:{n}", f"l:{n}",
+                   "l:7", "p:64", "p:64", "f:0.1", "p:64", "p:64", "p:empty", "p:empty", "p:0")
+    first = 0
+    for threads, blocks, rows, base, *_ in out[:-1]:
+        assert threads == 256 and rows == (1 << 33) + 24 * first and base == 7 + first
+        first += blocks
+    assert first == n and out[-1][:2] == [64, -(-n // 64)]
