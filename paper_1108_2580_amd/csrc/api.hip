@@ -32,6 +32,13 @@ int64_t even_chunk(int64_t d, int64_t chunk) {
   return ((d + n - 1) / n + 63) / 64 * 64;
 }
 
+int64_t interleaved(int64_t r, int64_t n) {
+  // the first `full` runs have per members, the others per - 1
+  const int64_t per = (n + kXcds - 1) / kXcds, full = n - (per - 1) * kXcds;
+  const int64_t rest = std::max<int64_t>(per - 1, 1), past = r - full * per;
+  return past < 0 ? r % per * kXcds + r / per : past % rest * kXcds + full + past / rest;
+}
+
 int64_t order_items(WorkItem *items, const int64_t *ptr, int64_t n_chunks, int64_t n) {
   std::stable_sort(items, items + n_chunks, [&](const WorkItem &x, const WorkItem &y) {
     return x.start - ptr[x.row] < y.start - ptr[y.row];
@@ -59,7 +66,6 @@ constexpr int64_t kWindowBytes = 4 << 20;  // one XCD's L2
 constexpr int64_t kMinWindows = 6;
 constexpr int64_t kMaxWindows = 64;
 constexpr int64_t kMinWindowChunk = 128;
-constexpr int64_t kXcds = 8;
 constexpr int64_t kDefaultWorkspace = 48LL << 30;
 // cap on the block-by-column count table of the device transpose
 constexpr int64_t kCscTableEntries = 1LL << 29;
@@ -435,7 +441,7 @@ als_status build_plan(als_ctx *ctx, SidePlan &P, const std::vector<int64_t> &ptr
 }
 
 // Order of each batch's chunks by the part of the fixed table that they read: the chunks,
-// sorted by their first index, are cut into kXcds equal runs, and the runs are interleaved, so
+// sorted by their first index, are cut into one run per XCD, and the runs are interleaved, so
 // that the chunks in flight on one XCD (workgroups go to the XCDs in turn) read one window of
 // the table that its L2 can hold.
 als_status order_chunks(als_ctx *ctx, SidePlan &P, const int32_t *d_idx, int64_t n_fixed) {
@@ -456,18 +462,14 @@ als_status order_chunks(als_ctx *ctx, SidePlan &P, const int32_t *d_idx, int64_t
     const WorkItem *src = P.gitems.data() + b.chunk_off;
     const int32_t *key = first.data() + b.chunk_off;
     std::vector<int64_t> at(kBuckets + 1, 0);
-    auto bucket = [&](int64_t q) { return (int64_t)key[q] * kBuckets / std::max<int64_t>(n_fixed, 1); };
+    auto bucket = [&](int64_t q) {
+      return (int64_t)key[q] * kBuckets / std::max<int64_t>(n_fixed, 1);
+    };
     for (int64_t q = 0; q < b.n_gchunks; ++q) at[bucket(q) + 1] += 1;
     for (int64_t k = 0; k < kBuckets; ++k) at[k + 1] += at[k];
     std::vector<WorkItem> out(b.n_gchunks);
-    const int64_t per = (b.n_gchunks + kXcds - 1) / kXcds, full = b.n_gchunks - (per - 1) * kXcds;
-    for (int64_t q = 0; q < b.n_gchunks; ++q) {
-      // rank r belongs to run x: the first `full` runs have per chunks, the others per - 1
-      const int64_t r = at[bucket(q)]++;
-      const int64_t x = r < full * per ? r / per : full + (r - full * per) / std::max<int64_t>(per - 1, 1);
-      const int64_t k = r < full * per ? r % per : (r - full * per) % std::max<int64_t>(per - 1, 1);
-      out[k * kXcds + x] = src[q];
-    }
+    for (int64_t q = 0; q < b.n_gchunks; ++q)
+      out[als::interleaved(at[bucket(q)]++, b.n_gchunks)] = src[q];
     std::copy(out.begin(), out.end(), P.gitems.begin() + b.chunk_off);
     HIP_OR_FAIL(ctx, hipMemcpy(P.d_gitems + b.chunk_off, out.data(),
                                sizeof(WorkItem) * b.n_gchunks, hipMemcpyHostToDevice));

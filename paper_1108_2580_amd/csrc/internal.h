@@ -37,6 +37,10 @@ int64_t even_chunk(int64_t d, int64_t chunk);
 // 48, D = 20 78 and 67; 1500 time bins of 6700, D = 10, 167 and 141; 4500 of 2200 191 and 161;
 // 2500 rows of 4000, D = 33, 412 and 375; 1000 of 5000, D = 100, 773 and 628.
 int64_t order_items(WorkItem *items, const int64_t *ptr, int64_t n_chunks, int64_t n);
+constexpr int64_t kXcds = 8;
+// Position of member r of n when they are cut into kXcds runs of even length and the runs
+// interleaved (api.hip): position p runs on XCD p mod kXcds.
+int64_t interleaved(int64_t r, int64_t n);
 
 // One row to solve, from its record (narrow widths) or its workspace slots (split rows).
 struct RowTask {

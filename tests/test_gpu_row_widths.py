@@ -5,7 +5,8 @@ has an instance of its own. Split rows come in several batches, whole rows besid
 Bars: those of the methods' own tests (relative row error 1e-4 against the fp64 oracle)."""
 import pytest
 
-from tests import test_gpu_bayes, test_gpu_bptf
+import workload
+from tests import test_gpu_bayes, test_gpu_bptf, test_gpu_parity, test_gpu_split, test_gpu_tensor
 from tests.test_gpu_split import test_gibbs_draw_of_split_rows as gibbs_draw
 
 pytestmark = pytest.mark.gpu
@@ -33,3 +34,25 @@ def test_gibbs(D):
     ptr, col, val = test_gpu_bayes.small_matrix(300, 200, 60 + D)
     test_gpu_bayes.check_gibbs_both_sides(300, 200, ptr, col, val, D, 0.05, 70 + D,
                                           label=f"whole{D}")
+
+
+@pytest.mark.parametrize("D", WIDTHS)
+def test_als(D):
+    test_gpu_parity.test_widths_with_split_rows_and_batches(D)
+    test_gpu_split.test_automatic_split(D)
+
+
+@pytest.mark.parametrize("D", WIDTHS)
+def test_weighted(D):
+    test_gpu_parity.test_weighted_widths_with_split_rows(D)
+    M, N, ptr, col, val, _, _ = test_gpu_split.edge_matrix(D)
+    U0, V0 = workload.init_factors(M, N, D, seed=5 + D)
+    test_gpu_parity.check_first_half_sweeps(
+        M, N, ptr, col, val, D, 0.065, U0, V0, label=f"wauto{D}",
+        weights=workload.rating_weights(col.size, seed=3 + D))
+
+
+@pytest.mark.parametrize("D", WIDTHS)
+def test_tensor(D):
+    test_gpu_tensor.test_tensor_split_rows_and_batches(D)
+    test_gpu_tensor.test_tensor_modes_match_oracle(D)

@@ -68,6 +68,25 @@ def test_gibbs_draw_of_split_rows(D):
     assert rel_rows(got, want).max() <= ROW_TOL
 
 
+def long_items(D, M, N=60):
+    """Items of hundreds to hundreds of thousands of ratings on a users' table of over 24 MB
+    (only items of under 1800 ratings get shorter chunks by it than without)."""
+    deg = np.full(M, 3)
+    deg[::50] = 0
+    deg[7] = N
+    return workload.make_custom(M, N, deg, seed=11 + D,
+                                item_weights=np.r_[np.arange(1, N) ** -2.5, 0.0])
+
+
+def windowed_chunks(d, D, M):
+    """The chunks that windows of 4 MB of the table cut rows of d > 512 ratings into."""
+    windows = M * (16 if D <= 16 else 32) * 4 >> 22
+    assert windows >= 6
+    d = d[d > 512]
+    chunk = np.minimum(256, np.maximum(128, -(-(d // windows) // 64) * 64))
+    return int((-(-d // chunk)).sum())
+
+
 @pytest.mark.parametrize("D,M", [(10, 450_000), (20, 250_000)])
 def test_windowed_chunks(D, M):
     """The items' fixed table is over 24 MB: the long items' chunks follow windows of it, the
@@ -75,16 +94,40 @@ def test_windowed_chunks(D, M):
     from paper_1108_2580_amd import ALS
 
     N = 60
-    deg = np.full(M, 3)
-    deg[::50] = 0
-    deg[7] = N
-    ptr, col, val = workload.make_custom(M, N, deg, seed=11 + D,
-                                         item_weights=np.r_[1.0 / np.arange(1, N), 0.0])
+    ptr, col, val = long_items(D, M)
     U0, V0 = workload.init_factors(M, N, D, seed=13 + D)
     with ALS(M, N, ptr, col, val, D) as als:
         st, whole = als.plan_stats("items"), als.plan_stats("users")
     d = np.bincount(col, minlength=N)
     assert whole["split_rows"] == 0 and st["split_rows"] == int((d > 512).sum()) > 10
-    assert st["chunks"] <= int((-(-d // 128))[d > 512].sum())
-    assert st["chunks"] >= int((-(-d // 256))[d > 512].sum())
+    assert st["chunks"] == windowed_chunks(d, D, M) > int((-(-d // 256))[d > 512].sum())
     check_first_half_sweeps(M, N, ptr, col, val, D, 0.065, U0, V0, label=f"windows{D}")
+
+
+@pytest.mark.parametrize("D,M", [(10, 450_000), (20, 250_000)])
+@pytest.mark.parametrize("method", ["weighted", "gibbs", "tensor", "bptf"])
+def test_windowed_chunks_of_other_methods(method, D, M):
+    """Weights, second indices, the prior image and the time plan, whose indices repeat within a
+    row, beside windowed chunks (a plan with windows is one batch)."""
+    from tests import test_gpu_bayes, test_gpu_bptf, test_gpu_tensor
+
+    N, bins = 60, 12
+    ptr, col, val = long_items(D, M)
+    print(f"windows {method} D={D}", flush=True)
+    if method == "weighted":
+        U0, V0 = workload.init_factors(M, N, D, seed=13 + D)
+        check_first_half_sweeps(M, N, ptr, col, val, D, 0.065, U0, V0, label=f"windows{D}",
+                                weights=workload.rating_weights(col.size, seed=17 + D))
+    elif method == "gibbs":
+        test_gpu_bayes.check_gibbs_both_sides(M, N, ptr, col, val, D, 0.05, 19 + D,
+                                              label=f"windows{D}")
+    elif method == "tensor":
+        rng = np.random.default_rng(23 + D)
+        t = rng.integers(0, bins - 1, size=col.size).astype(np.int32)
+        U, V, T = (rng.normal(m, s, size=(n, D)).astype(np.float32)
+                   for m, s, n in ((0, 0.5, M), (0, 0.5, N), (1, 0.3, bins)))
+        test_gpu_tensor.check_modes(M, N, bins, ptr, col, val, t, U, V, T, D, 0.065,
+                                    label=f"windows{D}")
+    else:
+        test_gpu_bptf.check_chain(M, N, bins, D, 29 + D, deg=(2, 4), empty_bins=(2,),
+                                  label=f"windows{D}")

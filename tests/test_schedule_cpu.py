@@ -71,3 +71,14 @@ def test_the_solve_adds_up_bounded_runs_of_residuals(rows, residuals, fused):
     fn = library("_ZN3als13solve_reducesEll", ctypes.c_int64, ctypes.c_int64)
     fn.restype = ctypes.c_bool
     assert fn(rows, residuals) == fused
+
+
+@pytest.mark.parametrize("n", [*range(1, 41), 1000, 4099])
+def test_interleaved_runs(n):
+    """Each position once, and the members on one XCD are consecutive and in order."""
+    fn = library("_ZN3als11interleavedEll", ctypes.c_int64, ctypes.c_int64)
+    at = np.array([fn(r, n) for r in range(n)])
+    assert sorted(at) == list(range(n))
+    for xcd in range(8):
+        members = [r for r in range(n) if at[r] % 8 == xcd]
+        assert (np.diff(members) == 1).all() and (np.diff(at[members]) == 8).all()
