@@ -64,9 +64,11 @@ typedef enum {
   ALS_MODE_TIME = 2   /* solve T (one row per time bin) with U and V fixed */
 } als_mode;
 
-/* Tunables of the degree-bucketed schedule. Zero fields select defaults; with threshold and
+/* Tunables of the degree-bucketed schedule. Zero fields select defaults. With threshold and
  * chunk both zero, a matrix too small to keep the GPU busy with rows of 8192 ratings gets a
- * finer split (down to 512 and 256). */
+ * finer split (down to 512 and 256 up to D = 20, 1024 and 512 above), into chunks of one length
+ * per row; and up to D = 20, where the fixed factors take 24 MiB or more, a split row's chunks
+ * get shorter (down to 128) so as to follow 4 MiB windows of them. */
 typedef struct {
   int32_t hub_threshold;   /* rows with more ratings are split into chunks (default 8192) */
   int32_t chunk;           /* ratings per chunk of a split row (default at most 4096) */

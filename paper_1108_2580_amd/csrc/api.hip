@@ -57,8 +57,8 @@ int64_t order_items(WorkItem *items, const int64_t *ptr, int64_t n_chunks, int64
 namespace {
 
 // Ratings per chunk of a split row; rows of more than two chunks' ratings are split.
-// kMaxChunk where the matrix fills the chip many times over, down to kMinChunk for smaller
-// ones (auto_split).
+// kMaxChunk where the matrix fills the chip many times over, down to kMinChunk (D <= 20) or
+// twice that for smaller ones (auto_split).
 constexpr int32_t kMaxChunk = 4096;
 constexpr int32_t kMinChunk = 256;
 // Chunks cut along windows of a large fixed table (Split).
@@ -244,7 +244,6 @@ size_t slot_bytes_of(const als_ctx *ctx) {
                          : als::slot_floats_rt(ctx->DP) * sizeof(float);
 }
 
-// Degree-ordered schedule of one side with hub rows split into chunks.
 // Row blocking of the device transpose: blocks of rows_per_blk rows whose per-column
 // counters (nblk x n_items int32) stay within kCscTableEntries.
 void csc_blocking(int64_t n_users, int64_t n_items, int64_t &rows_per_blk, int64_t &nblk) {
@@ -253,7 +252,9 @@ void csc_blocking(int64_t n_users, int64_t n_items, int64_t &rows_per_blk, int64
   nblk = (n_users + rows_per_blk - 1) / rows_per_blk;
 }
 
-// Wavefronts that the Gram kernel of a width keeps on a SIMD.
+// Wavefronts per SIMD that auto_split's share is reckoned with. The Gram kernels keep at least
+// as many on a SIMD (eight of one tile and up to seven of two or three run), but the chunk
+// lengths measured below are fractions of this share.
 int gram_waves(const als_ctx *ctx) {
   if (ctx->lane_solve) return 6;
   return ctx->DP <= 64 ? 5 : ctx->DP <= 80 ? 4 : ctx->DP <= 112 ? 3 : 2;
@@ -305,6 +306,7 @@ struct Split {
 
 als_status order_chunks(als_ctx *ctx, SidePlan &P, const int32_t *d_idx, int64_t n_fixed);
 
+// The degree-ordered schedule of one side, with the long rows split into chunks.
 // parity >= 0: only the rows s with s % 2 == parity, and those without ratings are
 // scheduled like the others (the time chain's bins, whose prior depends on the row).
 // d_idx: the side's fixed-row indices on the device; n_fixed: rows of the table they index.
@@ -899,8 +901,8 @@ als_status half_sweep_impl(als_ctx *ctx, als_side side, const float *fixed_facto
 }
 
 // The batches of one half-sweep on an already staged fixed side (d_fpad, and d_fpad2 for
-// tensor ALS; the staging launch clears the flag count), the entering-state reduction, the flag count and, on request, the
-// new-state RMSE.
+// tensor ALS; the staging launch clears the flag count), the entering-state reduction, the
+// flag count and, on request, the new-state RMSE.
 als_status run_sweep(als_ctx *ctx, const SweepSpec &sp, float lambda, float *out_factors,
                      double *rmse_out, const als::RowPrior &pr) {
   const SidePlan &P = ctx->plan[sp.plan];

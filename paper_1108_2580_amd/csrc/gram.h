@@ -40,7 +40,6 @@ __device__ __forceinline__ float row_ror(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + K, 0xF, 0xF, false));
 }
 
-// Sum over the 16 lanes of a row; every lane of the row receives the same value.
 // Sum of a double over the 64 lanes, in every lane: rotations within each 16-lane row
 // (both 32-bit halves moved by DPP), then the two swaps across the row groups. A fixed
 // order, so the result is the same on every run.
@@ -71,6 +70,7 @@ __device__ __forceinline__ double sum_wave_f64(double v) {
   return join(l32[0], h32[0]) + join(l32[1], h32[1]);
 }
 
+// Sum over the 16 lanes of a row; every lane of the row receives the same value.
 __device__ __forceinline__ float sum16(float v) {
   v += row_ror<8>(v);
   v += row_ror<4>(v);
@@ -135,10 +135,10 @@ template <int DP>
 struct RowCfg {
   static constexpr int T = DP / 16;
   static constexpr int NT = T * (T + 1) / 2;
-  // Steps per gathered block. Narrow rows gather a group at once. Wide rows keep two blocks of one step (four ratings) in flight:
-  // blocks of eight to two steps hid no more latency beside the other waves and took the
-  // registers of one of them (at eight tiles they spilled: tensor ALS, D = 128, 10.7 against
-  // 8.3 ms)
+  // Steps per gathered block. Narrow rows gather a group at once. Wide rows keep two blocks of
+  // one step (four ratings) in flight: blocks of eight to two steps hid no more latency beside
+  // the other waves and took the registers of one of them (at eight tiles they spilled: tensor
+  // ALS, D = 128, 10.7 against 8.3 ms)
   static constexpr int STEPS = T <= 2 ? 16 : 1;
   // group buffers in LDS
   static constexpr int BUFS = T <= 2 ? 1 : 2;
@@ -291,8 +291,8 @@ __device__ __forceinline__ void gather_block(float (&a)[STEPS][DP / 16], float (
 }
 
 // MFMA Gram update, right-hand side and per-step partial predictions (handed to put(step,
-// value)) of the gathered steps s0 .. s0 + STEPS - 1, in sub-blocks of up to four steps; sub-blocks past the
-// item's last step (steps of this group) are skipped. With AUG the right-hand side is
+// value)) of the gathered steps s0 .. s0 + STEPS - 1, in sub-blocks of up to four steps;
+// sub-blocks past the item's last step (steps of this group) are skipped. With AUG the right-hand side is
 // a column of the Gram and rhs is left alone. With WT (weighted ALS) the first MFMA
 // operand carries c f, so the tiles accumulate sum c f f^T (and, in the augmented
 // column, sum c r f); predictions use the unweighted rows.

@@ -125,7 +125,8 @@ hipError_t launch_stage_fixed(const float *F, int64_t n, float *Fp, const float 
 // Fused per-row normal equations, regularisation, Cholesky and solves; X is read
 // (entering state) and overwritten in place (rowsolve.hip). Exactly one of items and rows:
 //  - items: n_tasks gather items: chunks of split rows, whose partial normal equations go to
-//    their workspace slots, and whole rows, solved at once. Item i writes its entering-state squared residuals to sse[i].
+//    their workspace slots, and whole rows, solved at once. Item i writes its entering-state
+//    squared residuals to sse[i].
 //  - rows: n_tasks split rows, whose first slots launch_sum_slots has filled.
 // wts (here and below): per-rating weights aligned with idx / val for weighted ALS,
 // or null for plain ALS.

@@ -6,8 +6,8 @@
 // allows (float4 when D % 4 == 0, then float2, then float). A group of 4 or 8 lanes
 // shares a pair, so that each load instruction reads contiguous row segments (the
 // wave's 64 lanes touch 16 or 8 rows instead of 64), and the group's partial sums are
-// added by shuffles; rows of fewer than four loads take one lane per pair, eight
-// vectors per row in flight before any arithmetic. The dot
+// added by shuffles; rows of fewer than four loads take one lane per pair, which has
+// them all in flight before any arithmetic. The dot
 // product runs with fused multiply-adds in fp32 (in feature order for one lane per
 // pair; strided per lane, then a shuffle tree, for a group). Pairs whose
 // indices fall outside the factor tables give NaN and read nothing. With
@@ -21,6 +21,9 @@ namespace als {
 
 namespace {
 
+constexpr int kPairBlock = 256;
+constexpr int kGroupLoads = 4;  // loads a row from which on a group of lanes shares a pair
+
 // Floats per load: the widest that every row's alignment allows (16-byte aligned tables).
 int predict_vec(int D) { return D % 4 == 0 ? 4 : D % 2 == 0 ? 2 : 1; }
 
@@ -30,11 +33,8 @@ int predict_vec(int D) { return D % 4 == 0 ? 4 : D % 2 == 0 ? 2 : 1; }
 // 50 and 40, 13 111 and 42, 33 318 and 83, 50 286 and 105, 89 932 and 128, 127 1360 and 173.
 int predict_group(int D) {
   const int nv = D / predict_vec(D);
-  return nv >= 24 ? 8 : (nv >= 4 ? 4 : 1);
+  return nv >= 24 ? 8 : (nv >= kGroupLoads ? 4 : 1);
 }
-
-constexpr int kPairBlock = 256;
-constexpr int kVecInFlight = 8;
 
 template <int VW> struct Vec;
 template <> struct Vec<4> {
@@ -58,7 +58,8 @@ template <> struct Vec<1> {
   static __device__ __forceinline__ float fma_dot(T a, T b, float acc) { return fmaf(a, b, acc); }
 };
 
-// u . v over D features (D % VW == 0, both rows VW * 4-byte aligned), in feature order.
+// u . v over D features (D % VW == 0, fewer than kGroupLoads loads a row, both rows
+// VW * 4-byte aligned), in feature order.
 template <int VW>
 __device__ __forceinline__ float row_dot(const float *__restrict__ u, const float *__restrict__ v,
                                          int D) {
@@ -66,20 +67,18 @@ __device__ __forceinline__ float row_dot(const float *__restrict__ u, const floa
   const T *__restrict__ a = reinterpret_cast<const T *>(u);
   const T *__restrict__ b = reinterpret_cast<const T *>(v);
   const int nv = D / VW;
-  float acc = 0.f;
-  for (int c = 0; c < nv; c += kVecInFlight) {
-    T x[kVecInFlight], y[kVecInFlight];
+  T x[kGroupLoads - 1], y[kGroupLoads - 1];
 #pragma unroll
-    for (int k = 0; k < kVecInFlight; ++k) {
-      if (c + k < nv) {
-        x[k] = a[c + k];
-        y[k] = b[c + k];
-      }
+  for (int k = 0; k < kGroupLoads - 1; ++k) {
+    if (k < nv) {
+      x[k] = a[k];
+      y[k] = b[k];
     }
-#pragma unroll
-    for (int k = 0; k < kVecInFlight; ++k)
-      if (c + k < nv) acc = Vec<VW>::fma_dot(x[k], y[k], acc);
   }
+  float acc = 0.f;
+#pragma unroll
+  for (int k = 0; k < kGroupLoads - 1; ++k)
+    if (k < nv) acc = Vec<VW>::fma_dot(x[k], y[k], acc);
   return acc;
 }
 

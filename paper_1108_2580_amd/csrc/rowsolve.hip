@@ -129,11 +129,14 @@ __global__ __launch_bounds__(256) void k_sum_slots(const RowTask *__restrict__ r
 // Wavefronts per SIMD that the register allocation aims at. The factorisation is a chain of
 // dependent steps, so a SIMD needs several rows' chains at once; one step per gathered block
 // and the step partials in LDS leave room for them. Measured on 10M lognormal ratings, us per
-// sweep at two (three for 48 tiles' width) waves and now: D = 36 843 and 770, 50 1424 and
-// 1227, 64 1604 and 1512, 68 2049 and 1785, 92 2960 and 2690, 100 3600 and 3405 (where 41
-// registers spill). At eight tiles the accumulators alone take 144 of the 168 registers that
-// three waves leave (1127 spills); with an explicit right-hand side and the prior image the
-// bound spills around a hundred.
+// sweep at two waves (three at three tiles) and now: D = 36 843 and 770, 50 1424 and 1227, 64
+// 1604 and 1512, 68 2049 and 1785, 92 2960 and 2690, 100 3600 and 3405 (40 registers spill). At
+// seven tiles without the augmented column around a hundred spill and the third wave still pays
+// (6M uniform ratings, D = 112: 2745 and 2610, weighted 2845 and 2670); with the prior image on
+// top the bound stays at two. At eight tiles the accumulators alone take 144 of the 168 registers that
+// three waves leave (1127 spills). Where a side has about two rows per SIMD, all of like length,
+// the waves beyond two only unbalance the SIMDs: 2040 rows of 1000 ratings took 255 and 327 at
+// D = 100.
 template <int DP, bool AUG, bool BAYES>
 constexpr int kRowWaves = BAYES && !AUG              ? 2
                           : DP == 64                 ? 5
