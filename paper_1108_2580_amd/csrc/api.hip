@@ -45,9 +45,15 @@ int64_t order_items(WorkItem *items, const int64_t *ptr, int64_t n_chunks, int64
   });
   int32_t longest = 0;
   for (int64_t i = 0; i < n_chunks; ++i) longest = std::max(longest, items[i].len);
-  int64_t lead = 0;
-  if (n_chunks > 0)
-    while (n_chunks + lead < n && items[n_chunks + lead].len > longest) ++lead;
+  int64_t lead = 0, total = 0, behind = 0;
+  for (int64_t i = 0; i < n; ++i) {
+    total += items[i].len;
+    if (i >= n_chunks && items[i].len > longest)
+      ++lead;
+    else if (i >= n_chunks)
+      behind += items[i].len;
+  }
+  if (n_chunks == 0 || 4 * behind > total) return 0;
   std::rotate(items, items + n_chunks, items + n_chunks + lead);
   return lead;
 }

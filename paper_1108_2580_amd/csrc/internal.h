@@ -30,7 +30,10 @@ int64_t even_chunk(int64_t d, int64_t chunk);
 // starts first; returns their number. Behind the chunks, a few rows just under the splitting
 // threshold ran on alone at the end (2500 rows of about 4000 ratings, nine of them whole, D =
 // 33: 457 us a half-sweep behind, 412 ahead; of about 1200, 153 and 132; time bins of 3300
-// ratings, D = 10, 178 and 160; 1500 rows of 3300, D = 100, 856 and 774).
+// ratings, D = 10, 178 and 160; 1500 rows of 3300, D = 100, 856 and 774). Where shorter rows
+// hold over a quarter of the ratings they fill that end, and ahead the long rows' factorisations
+// fall together instead of beside the chunks (1M lognormal ratings, D = 64 290 us a sweep ahead
+// and 284 behind, D = 80 387 and 378): those keep the chunks first.
 // Chunks go by their depth in their row, so that those in flight read one part of the fixed
 // table, as whole rows walking it side by side do; row by row they spread over all of it. With
 // even_chunk, us a half-sweep row by row and by depth: 4000 rows of 750 ratings, D = 10 60 and
